@@ -13,6 +13,7 @@
 #include "internal.hpp"
 #include "wide.hpp"
 #include "conv_p.hpp"
+#include "conv_wgrad.hpp"
 
 using namespace ffdp;
 
@@ -773,8 +774,9 @@ int ffdp_conv3d_bwd_weight(const uint16_t* xa, const uint16_t* xb, const float* 
     const size_t need = (size_t)conv_wgrad_plan(g).part_floats * sizeof(float);
     if (!ws || ws_bytes < need) return fail(FFDP_ERR_WORKSPACE, "workspace of %zu bytes required (got %zu)", need, ws_bytes);
     if (misaligned_n(ws, 4)) return fail(FFDP_ERR_ALIGN, "workspace must be 4-byte aligned");
-    return hip_status(conv_bwd_weight_launch(g, (const unsigned short*)xa, (const unsigned short*)xb, dy,
-                                             (const unsigned short*)y, slope, dw, db, (float*)ws, (hipStream_t)stream),
+    return hip_status(conv_wgrad_launch(g, (const unsigned short*)xa, (const unsigned short*)xb, dy,
+                                        (const unsigned short*)y, slope, nullptr, dw, db, (float*)ws,
+                                        (hipStream_t)stream),
                       "ffdp_conv3d_bwd_weight");
 }
 
@@ -790,8 +792,8 @@ int ffdp_conv3d_bwd_weight_bf16(const uint16_t* xa, const uint16_t* xb, const ui
     const size_t need = (size_t)conv_wgrad_plan(g).part_floats * sizeof(float);
     if (!ws || ws_bytes < need) return fail(FFDP_ERR_WORKSPACE, "workspace of %zu bytes required (got %zu)", need, ws_bytes);
     if (misaligned_n(ws, 4)) return fail(FFDP_ERR_ALIGN, "workspace must be 4-byte aligned");
-    return hip_status(conv_bwd_weight_p_launch(g, (const unsigned short*)xa, (const unsigned short*)xb,
-                                               (const unsigned short*)p, dw, db, (float*)ws, (hipStream_t)stream),
+    return hip_status(conv_wgrad_launch(g, (const unsigned short*)xa, (const unsigned short*)xb, nullptr, nullptr,
+                                        0.0f, (const unsigned short*)p, dw, db, (float*)ws, (hipStream_t)stream),
                       "ffdp_conv3d_bwd_weight_bf16");
 }
 

@@ -145,22 +145,11 @@ struct ConvGeom {
     int stride;      // 1 or 2
     int ups;         // part a stored at half resolution, nearest x2
 };
-struct ConvWgradPlan {
-    long long VC;          // output voxels per chunk (bias partials; the voxel-chunk kernels)
-    int nchunks;
-    long long part_floats;  // workspace floats
-    int rows;              // 1: the row-segment kernel (stride 1, Cout <= 64)
-    long long VS;          // row segments of 32 output voxels per chunk (row-segment kernel)
-};
-ConvWgradPlan conv_wgrad_plan(const ConvGeom& g);
 hipError_t conv_fwd_launch(const ConvGeom& g, const unsigned short* xa, const unsigned short* xb,
                            const unsigned short* w, const float* bias, int act, float slope, unsigned short* ybf,
                            float* yf, hipStream_t st);
 hipError_t conv_bwd_data_launch(const ConvGeom& g, const float* dy, const unsigned short* y, float slope,
                                 const unsigned short* wt, float* dx, int accumulate, hipStream_t st);
-hipError_t conv_bwd_weight_launch(const ConvGeom& g, const unsigned short* xa, const unsigned short* xb,
-                                  const float* dy, const unsigned short* y, float slope, float* dw, float* db,
-                                  float* part, hipStream_t st);
 hipError_t cast_bf16_launch(const float* x, long long n, unsigned short* y, hipStream_t st);
 hipError_t weight_prep_launch(const float* w, int Cout, int Cin, unsigned short* wbf, unsigned short* wt,
                               hipStream_t st);

@@ -20,8 +20,8 @@ OUT = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libffdp.so")
 ARCH = "gfx950"
 
-SOURCES = ["lncc.hip", "lncc_wide.hip", "mi.hip", "elementwise.hip", "smooth.hip", "conv3d.hip", "conv3d_wgrad.hip",
-           "api.cpp"]
+SOURCES = ["lncc.hip", "lncc_wide.hip", "mi.hip", "elementwise.hip", "smooth.hip", "conv3d.hip", "conv3d_tile.hip",
+           "conv3d_dgrad2.hip", "conv3d_wgrad.hip", "api.cpp"]
 
 # Packed fp32 instructions are switched off (ordinary float code only).
 HIPFLAGS = ["-O3", "-std=c++17", f"--offload-arch={ARCH}", "-fPIC", "-Wall",

@@ -1,0 +1,764 @@
+// 3x3x3 BF16 convolution, pad 1, channels-last (gfx950): the forward pass
+// (stride 1 or 2, optionally over the concatenation of a nearest x2 upsampled
+// part a and a part b) and, with the taps mirrored, the input gradient of a
+// stride-1 layer.  FP32 accumulation on v_mfma_f32_16x16x32_bf16.
+//
+// A block takes 16 output voxels in x, WR * RW rows in y and WN tiles of 16
+// output channels, and streams along z.  Wave (wr, wn) owns RW rows of one
+// channel tile.  A step stages one input slice, with its halo, of one group of
+// up to 32 channels in LDS; it adds what that slice gives to all the output
+// slices it touches (3 at stride 1, 2 at stride 2), whose sums stay in
+// registers, so a slice is read once and not once per output slice.
+//
+// Operands: weights are A (rows: output channels), voxels are B (columns), so
+// a lane of the result holds 4 consecutive channels of one voxel and stores
+// them together.  For each x shift the fragments of the wave's input rows are
+// read from LDS once and held; each weight fragment then meets RW of them: 57
+// reads for 216 MFMAs at stride 1 and RW = 8, where one read per MFMA would
+// already be twice what LDS delivers at full matrix rate.
+//
+// Two kernels.  conv_tile_kernel keeps LDS units of 8 channels as [chunk][row]
+// [x] (the 16 lanes of a fragment read 256 consecutive bytes) and stages
+// through registers.  Its K steps of 32: a full group is 27 (tap) steps of 32
+// channels; a group of up to 16 channels pairs taps (dx 0 and 1 of a row; dx 2
+// of two rows: 15 steps, 13.5 being the least); one of up to 8 channels takes
+// dx 0, 1, 2 in one step (9 steps).  Lanes that a pattern leaves over multiply
+// zeros by zeros, so an infinite value reaches only the sums it belongs to.
+// Weights are resident in LDS where 27 taps of the layer's channels fit beside
+// the slices (at most 32 + 16 channels).  conv_wide_kernel takes the stride-1
+// layers with more: weights and slices go to LDS directly, a third of a
+// group's weights at a time.
+//
+// Bound and rates, clinical batch of 4 (ms, against a kernel that gathered
+// both operands per lane from global memory): matrix issue for 48 -> 16 at full
+// resolution, 4.85 -> 1.04 (1090 TFLOP/s; MFMA busy 0.56 of the SIMD cycles),
+// 96 -> 32 1.73 -> 0.65, 192 -> 64 0.82 -> 0.40; staging and stores for the
+// thin layers, 4 -> 16 1.38 -> 0.48, 16 -> 4 2.02 -> 0.49, 16 -> 32 stride 2
+// 0.53 -> 0.32 (2.2 to 2.9 TB/s).  Input gradients: 16 -> 48 3.66 -> 1.68 (3.7
+// TB/s, the fp32 gradient's write), 32 -> 96 1.56 -> 0.73, 64 -> 192 1.25 ->
+// 0.41, 4 -> 16 1.09 -> 0.54.  One clinical volume, 192 -> 64: 0.22 -> 0.13.
+#include "conv_p.hpp"
+#include "conv_tile.hpp"
+#include "device.hpp"
+#include "internal.hpp"
+
+namespace ffdp {
+
+namespace {
+
+// Channels of a launch of the tile kernel: one group of up to 16, one of up to
+// 8, an upsampled part a of up to 32 and a part b of up to 16 (weights
+// resident in LDS for these), or groups of 32 (the last zero-padded; weights
+// read through L2), part a upsampled or not.
+enum { TC_FULL = 0, TC_FULL_UPS = 1, TC_HALF = 2, TC_QUARTER = 3, TC_MIX = 4 };
+__host__ __device__ constexpr bool tc_resident(int kind) { return kind >= TC_HALF; }
+
+// a step's K pattern by its part, and whether part a is upsampled
+__host__ __device__ constexpr int tc_type(int kind, int part)
+{
+    return kind == TC_MIX ? (part ? TC_HALF : TC_FULL) : tc_resident(kind) ? kind : TC_FULL;
+}
+__host__ __device__ constexpr bool tc_ups(int kind) { return kind == TC_MIX || kind == TC_FULL_UPS; }
+__host__ __device__ constexpr int tc_frags(int type) { return type == TC_FULL ? 27 : type == TC_HALF ? 15 : 9; }
+
+struct TcGroup {
+    int part, c0, f0;  // part (0: a), first channel in it, weight fragments before the group
+};
+
+template <int S, int RW, int WR, int WN, int KIND>
+struct TcTile {
+    static constexpr int NT = 64 * WR * WN;
+    static constexpr int YT = WR * RW;
+    static constexpr int XW = S * 15 + 3, XP = S == 1 ? XW : XW + 1;  // columns and row pitch
+    static constexpr int XH = S * (YT - 1) + 3;
+    static constexpr int UXW = S == 1 ? 10 : 17;                      // of an upsampled part
+    static constexpr int UXH = S == 1 ? YT / 2 + 2 : YT + 1;
+    // plane of one chunk in 16-byte units, 2 (mod 8) so that the chunks of a voxel start in different banks
+    static constexpr int pad(int u) { return u + ((10 - u % 8) % 8); }
+    static constexpr int PL = pad(XP * XH), UPL = pad(UXW * UXH);
+    // staged units of a step and part, and per thread
+    static constexpr int units(int part)
+    {
+        return (tc_ups(KIND) && part == 0 ? UXW * UXH : XW * XH) * (tc_type(KIND, part) == TC_FULL ? 4 : 2);
+    }
+    static constexpr int UA = units(0), UB = units(1);
+    // v / w = v * div(w) >> 16 for every staged v
+    static constexpr int div(int w) { return (65536 + w - 1) / w; }
+    static constexpr bool div_ok(int w, int n)
+    {
+        for (int v = 0; v < n; ++v)
+            if (v * div(w) >> 16 != v / w || v * div(w) >= 1 << 30) return false;
+        return true;
+    }
+    static constexpr int NU = ((UA > UB ? UA : UB) + NT - 1) / NT;
+    // 16-byte units of a part's slice buffer
+    static constexpr int buf(int part)
+    {
+        return (tc_ups(KIND) && part == 0 ? UPL : PL) * (tc_type(KIND, part) == TC_FULL ? 4 : 2);
+    }
+    static constexpr int XR = S * (RW - 1) + 3;                       // input rows of a wave
+    static_assert(div_ok(XW, NU * NT) && div_ok(UXW, NU * NT), "row of a unit");
+    static_assert(RW % 2 == 0, "an upsampled part needs even row offsets");
+};
+
+// tap and channel chunk of lane group kg in fragment f of a group; false: the pattern leaves the lane over
+template <int TYPE>
+__device__ __forceinline__ bool tc_tap(int f, int kg, int& tap, int& chunk)
+{
+    int dz, dy, dx;
+    bool ok = true;
+    if (TYPE == TC_FULL) {
+        dx = f / 9; dz = (f / 3) % 3; dy = f % 3; chunk = kg;
+    } else if (TYPE == TC_HALF) {
+        chunk = kg & 1;
+        if (f < 9) {
+            dz = f / 3; dy = f % 3; dx = kg >> 1;
+        } else if (f < 12) {
+            dz = f - 9; dx = 2; dy = kg >> 1;
+        } else {
+            dz = f - 12; dx = 2; dy = 2; ok = kg >= 2;
+        }
+    } else {
+        dz = f / 3; dy = f % 3; dx = kg; chunk = 0; ok = kg < 3;
+    }
+    tap = ok ? dz * 9 + dy * 3 + dx : 0;
+    return ok;
+}
+
+// 8 weights of the lane (zeros outside the channels), any channel count that is a multiple of 4
+template <int TYPE, bool FLIP>
+__device__ __forceinline__ uint4 tc_weight(const TcArgs& a, const TcGroup& gr, int f, int kg, int n)
+{
+    const int C = gr.part ? a.Cb : a.Ca, Cin = a.Ca + a.Cb;
+    int tap, chunk;
+    const bool ok = tc_tap<TYPE>(f, kg, tap, chunk) && n < a.Nout;
+    const int c = gr.c0 + 8 * chunk;
+    const gptr p = as_global(a.w) + ((size_t)n * 27 + (FLIP ? 26 - tap : tap)) * Cin + (gr.part ? a.Ca : 0) + c;
+    const gptr z = as_global(&tc_zero);
+    const uint2 lo = ld8(ok && c + 4 <= C ? p : z), hi = ld8(ok && c + 8 <= C ? p + 4 : z);
+    return make_uint4(lo.x, lo.y, hi.x, hi.y);
+}
+
+// Output slice zo of a wave's RW rows: 4 channels (co ..) of voxel x per lane and row.
+template <int RW, bool GRAD>
+__device__ __forceinline__ void tc_finish(const TcArgs& a, const f4v (&v0)[RW], int bn, int zo, int y0, int x, int co)
+{
+    const bool mine = co < a.Nout && x < a.Wo;
+    f4v b4 = f4v{0.f, 0.f, 0.f, 0.f};
+    if (!GRAD && a.bias && mine) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) b4[e] = a.bias[co + e];
+    }
+#pragma unroll
+    for (int r = 0; r < RW; ++r) {
+        const int y = y0 + r;
+        if (!mine || y >= a.Ho) continue;
+        const size_t o = ((((size_t)bn * a.Do + zo) * a.Ho + y) * a.Wo + x) * a.Nout + co;
+        f4v v = v0[r];
+        if (GRAD) {
+            f32x4_a4* const d = reinterpret_cast<f32x4_a4*>(a.yf + o);
+            if (a.accumulate) {
+                const f32x4_a4 old = *d;
+                v[0] += old.x; v[1] += old.y; v[2] += old.z; v[3] += old.w;
+            }
+            *d = f32x4_a4{v[0], v[1], v[2], v[3]};
+        } else {
+            v += b4;
+            if (a.act) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.0f ? v[e] : v[e] * a.slope;
+            }
+            if (a.ybf) *reinterpret_cast<bf4v_a8*>(a.ybf + o) = __builtin_convertvector(v, bf4v_a8);
+            if (a.yf) *reinterpret_cast<f32x4_a4*>(a.yf + o) = f32x4_a4{v[0], v[1], v[2], v[3]};
+        }
+    }
+}
+
+// After the last step of input slice k: store the output slice that it completes and move the others up.
+template <int S, int RW, bool GRAD, int SL>
+__device__ __forceinline__ void tc_advance(const TcArgs& a, f4v (&acc)[SL][RW], int k, int bn, int z0, int y0, int x0,
+                                           int n0)
+{
+    if (S == 2 && k % 2 != 0) return;
+    if (k >= 2) {
+        const int lane = opaque(threadIdx.x & 63);
+        tc_finish<RW, GRAD>(a, acc[S == 1 ? SL - 1 : 0], bn, z0 + (S == 1 ? k - 2 : k / 2 - 1), y0, x0 + (lane & 15),
+                            n0 + 4 * (lane >> 4));
+    }
+#pragma unroll
+    for (int r = 0; r < RW; ++r) {
+        if (S == 1) {
+            acc[SL - 1][r] = acc[1][r];
+            acc[1][r] = acc[0][r];
+            acc[0][r] = f4v{0.f, 0.f, 0.f, 0.f};
+        } else {
+            acc[0][r] = acc[1][r];
+            acc[1][r] = f4v{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+}
+
+// Does tap dz of a block's input slice k meet one of its nz output slices?
+template <int S>
+__device__ __forceinline__ bool tc_used(int k, int dz, int nz)
+{
+    const int t = k - dz;
+    return t >= 0 && t % S == 0 && t / S < nz;
+}
+// accumulator of tap dz
+template <int S>
+__host__ __device__ constexpr int tc_slot(int dz) { return S == 1 ? dz : (dz == 0 ? 1 : 0); }
+
+template <int S, int RW, int WR, int WN, int KIND, bool FROMDY, bool GRAD>
+__global__ void __launch_bounds__(64 * WR * WN, 2) conv_tile_kernel(TcArgs a)
+{
+    using T = TcTile<S, RW, WR, WN, KIND>;
+    constexpr int SL = S == 1 ? 3 : 2;  // output slices in flight
+    constexpr bool TWO = tc_ups(KIND);  // the parts stage differently
+    constexpr bool RES = tc_resident(KIND);
+    constexpr int TYPE_A = tc_type(KIND, 0), TYPE_B = tc_type(KIND, 1);
+    extern __shared__ uint4 lds[];
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wn = wave % WN, wr = wave / WN;
+    int q = xcd_remap(blockIdx.x, a.nblocks);  // channel blocks of one column side by side
+    const int n0 = (q % a.nnb) * WN * 16; q /= a.nnb;
+    const int x0 = (q % a.nx) * 16; q /= a.nx;
+    const int y0 = (q % a.ny) * T::YT; q /= a.ny;
+    const int z0 = (q % a.nz) * a.zlen;
+    const int bn = q / a.nz;
+    const int z1 = min(a.Do, z0 + a.zlen);
+    const int nk = S * (z1 - z0 - 1) + 3;  // input slices S z0 - 1 ..
+    // by the run-time count of groups: with the part a known constant of the
+    // step the compiler threads the steps into one another and spills
+    auto group = [&](int g) {
+        if (KIND == TC_HALF || KIND == TC_QUARTER || g < a.na) return TcGroup{0, 32 * g, tc_frags(TYPE_A) * g};
+        return TcGroup{1, 32 * (g - a.na), tc_frags(TYPE_A) * a.na + tc_frags(TYPE_B) * (g - a.na)};
+    };
+
+    for (int p = tid; RES && p < WN * a.nfrag * 64; p += T::NT) {
+        const int l = p & 63, fr = p >> 6, tile = fr / a.nfrag, f = fr - tile * a.nfrag;
+        const int n = n0 + tile * 16 + (l & 15), fa = tc_frags(TYPE_A);
+        if (f < fa) lds[p] = tc_weight<TYPE_A, GRAD>(a, group(0), f, l >> 4, n);
+        else lds[p] = tc_weight<TYPE_B, GRAD>(a, group(1), f - fa, l >> 4, n);
+    }
+
+    const bool active = n0 + wn * 16 < a.Nout && y0 + wr * RW < a.Ho;  // of the wave
+    f4v acc[SL][RW];
+#pragma unroll
+    for (int s = 0; s < SL; ++s)
+#pragma unroll
+        for (int r = 0; r < RW; ++r) acc[s][r] = f4v{0.f, 0.f, 0.f, 0.f};
+
+    // staging of (slice k, group): units of 8 channels, channel chunks fastest.
+    // The parts differ in uniform values only, so that there is one copy of it.
+    uint4 xr[T::NU];
+    auto load = [&](int k, const TcGroup& gr) __attribute__((always_inline)) {
+        const bool ups = TWO && gr.part == 0;
+        const int lq = (ups || !TWO ? TYPE_A : TYPE_B) == TC_FULL ? 2 : 1, nun = ups || !TWO ? T::UA : T::UB;
+        const int C = gr.part ? a.Cb : a.Ca;
+        const gptr src = as_global(gr.part ? a.xb : a.xa);
+        const int us = ups ? 1 : 0;
+        const int sW = a.Wi >> us, sH = a.Hi >> us, sD = a.Di >> us;
+        const int bx = (S * x0 >> us) - 1, by = (S * y0 >> us) - 1, zi = (S * z0 - 1 + k) >> us;
+        const bool zok = (unsigned)zi < (unsigned)sD;
+        const size_t base = ((size_t)bn * sD + (zok ? zi : 0)) * ((size_t)sH * sW) * C;
+        const int w = ups ? T::UXW : T::XW, rw = ups ? T::div(T::UXW) : T::div(T::XW);
+        const bool c8 = !RES || KIND == TC_MIX || (C & 7) == 0;
+        const int t0 = opaque(tid);
+        const gptr z = as_global(&tc_zero);
+#pragma unroll
+        for (int u = 0; u < T::NU; ++u) {
+            if (u * T::NT < nun) {
+                const int p = t0 + T::NT * u;
+                const int v = p >> lq, c = gr.c0 + 8 * (p & ((1 << lq) - 1));
+                const int vy = (int)(__umul24(v, rw) >> 16), vx = v - (int)__umul24(vy, w);
+                const int X = bx + vx, Y = by + vy;
+                const bool ok = zok && p < nun && c < C && (unsigned)X < (unsigned)sW && (unsigned)Y < (unsigned)sH;
+                const size_t o = base + (size_t)((unsigned)(Y * sW + X)) * C;
+                uint4 r = make_uint4(0u, 0u, 0u, 0u);
+                if constexpr (FROMDY) {
+                    if (ok) r = p_from_dy8(a.dy, a.y, a.slope, o, c, C);
+                } else if (c8) {
+                    r = ld16(ok ? src + o + c : z);
+                } else {
+                    const uint2 lo = ld8(ok ? src + o + c : z), hi = ld8(ok && c + 8 <= C ? src + o + c + 4 : z);
+                    r = make_uint4(lo.x, lo.y, hi.x, hi.y);
+                }
+                xr[u] = r;
+            }
+        }
+    };
+    auto store = [&](uint4* xd, const TcGroup& gr) __attribute__((always_inline)) {
+        const bool ups = TWO && gr.part == 0;
+        const int lq = (ups || !TWO ? TYPE_A : TYPE_B) == TC_FULL ? 2 : 1, nun = ups || !TWO ? T::UA : T::UB;
+        const int t0 = opaque(tid);
+#pragma unroll
+        for (int u = 0; u < T::NU; ++u) {
+            const int p = t0 + T::NT * u;
+            const int v = p >> lq, ch = p & ((1 << lq) - 1);
+            int d = v;
+            if (S == 2 && !ups) {  // even columns, then odd ones: a fragment's lanes stay consecutive
+                const int vy = v / T::XW, vx = v - vy * T::XW;
+                d = vy * T::XP + (vx & 1) * 17 + (vx >> 1);
+            }
+            if (p < nun) xd[ch * (ups ? T::UPL : T::PL) + d] = xr[u];
+        }
+    };
+    using std::integral_constant;
+
+    // one step of the wave with resident weights: everything slice k of the group gives
+    auto compute = [&](const uint4* xb, const TcGroup& gr, int k, auto type_c, auto ups_c) __attribute__((always_inline)) {
+        constexpr int TYPE = decltype(type_c)::value;
+        constexpr bool UPS = decltype(ups_c)::value;
+        constexpr int RP = UPS ? T::UXW : T::XP, PL = UPS ? T::UPL : T::PL;
+        const int lane = opaque(threadIdx.x & 63), li = lane & 15, kg = lane >> 4;
+        auto xs = [&](int dx) {
+            if (UPS) return (S * li + dx + 1) >> 1;
+            if (S == 1) return li + dx;
+            return (dx & 1) * 17 + li + (dx >> 1);
+        };
+        // LDS row of input row r (of the wave), in RP units
+        auto xrow = [](int r) { return UPS ? (r + 1) >> 1 : r; };
+        const uint4* const xw = xb + (UPS ? (S * RW * wr) / 2 : S * RW * wr) * RP;
+
+        const uint4* const wl = lds + (wn * a.nfrag + gr.f0) * 64 + lane;
+        const int n = min(n0 + wn * 16 + li, a.Nout - 1), cw = gr.c0 + 8 * kg, C = gr.part ? a.Cb : a.Ca;
+        const gptr wg = as_global(a.w) + (size_t)n * 27 * (a.Ca + a.Cb) + (gr.part ? a.Ca : 0) + cw;
+        auto weight = [&](int f) {
+            if (RES) return wl[f * 64];
+            const int tap = (f / 3) % 3 * 9 + f % 3 * 3 + f / 9;
+            return ld16(cw < C ? wg + (GRAD ? 26 - tap : tap) * (a.Ca + a.Cb) : as_global(&tc_zero));
+        };
+
+        constexpr int NB = TYPE == TC_FULL ? 9 : TYPE == TC_HALF ? 5 : 3;  // blocks of 3 weight fragments
+        constexpr int PD = RES ? 1 : 2;                                    // blocks loaded ahead
+        uint4 w[PD + 1][3];
+#pragma unroll
+        for (int b = 0; b < PD; ++b)
+#pragma unroll
+            for (int e = 0; e < 3; ++e)
+                if (RES || tc_used<S>(k, b % 3, z1 - z0)) w[b][e] = weight(3 * b + e);
+        uint4 X[T::XR];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            // keep the reads of later blocks out of this one (registers)
+            __builtin_amdgcn_sched_barrier(0);
+            if (b + PD < NB && (RES || tc_used<S>(k, (b + PD) % 3, z1 - z0)))  // what no output slice needs is not fetched
+#pragma unroll
+                for (int e = 0; e < 3; ++e) w[(b + PD) % (PD + 1)][e] = weight(3 * (b + PD) + e);
+            if (TYPE != TC_HALF || b < 3) {
+                // blocks of (x pattern, dz), one fragment per dy
+                if (b % 3 == 0) {
+                    const uint4* p;
+                    if (TYPE == TC_FULL) p = xw + kg * PL + xs(b / 3);
+                    else if (TYPE == TC_HALF) p = xw + (kg & 1) * PL + xs(kg >> 1);
+                    else p = xw + (kg == 3 ? PL : 0) + xs(kg == 3 ? 0 : kg);
+#pragma unroll
+                    for (int r = 0; r < T::XR; ++r) X[r] = p[xrow(r) * RP];
+                }
+                const int dz = b % 3;
+                if (tc_used<S>(k, dz, z1 - z0)) {
+#pragma unroll
+                    for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+                        for (int yo = 0; yo < RW; ++yo)
+                            acc[tc_slot<S>(dz)][yo] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                as_bf8(w[b % (PD + 1)][dy]), as_bf8(X[S * yo + dy]), acc[tc_slot<S>(dz)][yo], 0, 0, 0);
+                }
+            } else if (b == 3) {
+                // dx = 2 of rows r and r + 1: taps dy = 0, 1 of every dz
+                const uint4* const p = xw + (kg & 1) * PL + xs(2);
+#pragma unroll
+                for (int r = 0; r < T::XR - 1; ++r) {
+                    // an upsampled part's rows r, r + 1 are one coarse row for odd r
+                    const int hi = xrow(r + 1) - xrow(r);
+                    X[r] = p[xrow(r) * RP + (hi ? (kg >> 1) * RP : 0)];
+                }
+#pragma unroll
+                for (int dz = 0; dz < 3; ++dz)
+                    if (tc_used<S>(k, dz, z1 - z0))
+#pragma unroll
+                        for (int yo = 0; yo < RW; ++yo)
+                            acc[tc_slot<S>(dz)][yo] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                as_bf8(w[b % (PD + 1)][dz]), as_bf8(X[S * yo]), acc[tc_slot<S>(dz)][yo], 0, 0, 0);
+            } else {
+                // dx = 2, dy = 2 of every dz: the upper lanes of rows r + 1, r + 2
+                const unsigned m = kg >= 2 ? 0xffffffffu : 0u;
+#pragma unroll
+                for (int yo = 0; yo < RW; ++yo) {
+                    uint4 v = X[S * yo + 1];
+                    v.x &= m; v.y &= m; v.z &= m; v.w &= m;
+                    X[S * yo + 1] = v;
+                }
+#pragma unroll
+                for (int dz = 0; dz < 3; ++dz)
+                    if (tc_used<S>(k, dz, z1 - z0))
+#pragma unroll
+                        for (int yo = 0; yo < RW; ++yo)
+                            acc[tc_slot<S>(dz)][yo] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                as_bf8(w[b % (PD + 1)][dz]), as_bf8(X[S * yo + 1]), acc[tc_slot<S>(dz)][yo], 0, 0, 0);
+            }
+        }
+    };
+
+    // A step's data are loaded while the step two before runs, and written to
+    // LDS as the one before begins: the loads have a whole step to arrive, and
+    // waiting for them does not wait for that step's output.
+    const int nsteps = nk * a.ng;
+    load(0, group(0));
+    store(lds + a.buf[0], group(0));
+    int kl = a.ng > 1 ? 0 : 1, gl = a.ng > 1 ? 1 : 0;  // the step to load next
+    if (nsteps > 1) load(kl, group(gl));
+    __syncthreads();
+    int par = 0, step = 0;
+    for (int k = 0; k < nk; ++k) {
+#pragma unroll 1
+        for (int gi = 0; gi < a.ng; ++gi, ++step) {
+            const TcGroup gr = group(gi);
+            const bool last = gi + 1 == a.ng;
+            if (step + 1 < nsteps) store(lds + a.buf[par ^ 1], group(gl));
+            if (++gl == a.ng) { gl = 0; ++kl; }
+            if (step + 2 < nsteps) load(kl, group(gl));
+            __builtin_amdgcn_sched_barrier(0);
+            if (active) {
+                const uint4* const xb = lds + a.buf[par];
+                if (!TWO || gr.part == 0)
+                    compute(xb, gr, k, integral_constant<int, TYPE_A>{}, std::bool_constant<TWO>{});
+                else
+                    compute(xb, gr, k, integral_constant<int, TYPE_B>{}, std::bool_constant<false>{});
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            par ^= 1;
+            if (last && active) tc_advance<S, RW, GRAD>(a, acc, k, bn, z0, y0 + wr * RW, x0, n0 + wn * 16);
+            __syncthreads();
+        }
+    }
+}
+
+// Wide layers: groups of 32 channels, weights staged with the slices.
+//
+// LDS keeps units of 8 channels, 4 to a voxel (or to a weight row), the chunk
+// XORed with bits of the position, so that both the 16 lanes of a fragment
+// (one chunk of consecutive voxels or rows) and the lanes of a load (the
+// chunks of a voxel) fall in different banks.  Loads go to LDS directly; a
+// sub-step is one x shift of a (slice, group): 9 weight fragments per tile
+// (the next ones are in flight meanwhile) against the wave's input rows.
+template <int S, int RW, int WR, int WN>
+struct WdTile {
+    static constexpr int NT = 64 * WR * WN, YT = WR * RW;
+    static constexpr int XW = S * 15 + 3, XP = S == 1 ? 18 : 34, XH = S * (YT - 1) + 3;
+    static constexpr int UXW = S == 1 ? 10 : 17, UXP = S == 1 ? 10 : 18, UXH = S == 1 ? YT / 2 + 2 : YT + 1;
+    static constexpr int XU = XH * XP * 4, UXU = UXH * UXP * 4;  // units of a slice
+    static constexpr int XB = (XU > UXU ? XU : UXU);             // ... of a buffer
+    static constexpr int WB = WN * 9 * 64;
+    static constexpr int LDS = 2 * (XB + WB) * 16;
+    static constexpr int NU = (XU + NT - 1) / NT, XR = S * (RW - 1) + 3;
+    static constexpr int div(int w) { return (65536 + w - 1) / w; }
+    static constexpr bool div_ok(int w, int n)
+    {
+        for (int v = 0; v < n; ++v)
+            if (v * div(w) >> 16 != v / w || v * div(w) >= 1 << 30) return false;
+        return true;
+    }
+    static_assert(div_ok(XP, NU * NT / 4) && div_ok(UXP, NU * NT / 4), "row of a unit");
+    static_assert(XP % 8 == 2 && UXP % 8 == 2, "the XOR pattern moves by one per row");
+    static_assert(LDS <= 160 * 1024, "LDS");
+};
+
+typedef __attribute__((address_space(3))) void* ldsptr;
+
+template <int S, int RW, int WR, int WN, bool TWO, bool C8, bool FROMDY, bool GRAD>
+__global__ void __launch_bounds__(64 * WR * WN, 2) conv_wide_kernel(TcArgs a)
+{
+    using T = WdTile<S, RW, WR, WN>;
+    constexpr int SL = S == 1 ? 3 : 2;
+    extern __shared__ uint4 lds[];
+    uint4* const xs = lds;              // [2][XB]
+    uint4* const ws = lds + 2 * T::XB;  // [2][WB]
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wn = wave % WN, wr = wave / WN;
+    int q = xcd_remap(blockIdx.x, a.nblocks);
+    const int n0 = (q % a.nnb) * WN * 16; q /= a.nnb;
+    const int x0 = (q % a.nx) * 16; q /= a.nx;
+    const int y0 = (q % a.ny) * T::YT; q /= a.ny;
+    const int z0 = (q % a.nz) * a.zlen;
+    const int bn = q / a.nz;
+    const int nz = min(a.Do, z0 + a.zlen) - z0;
+    const int nk = S * (nz - 1) + 3;
+    const int Cin = a.Ca + a.Cb;
+    const bool active = n0 + wn * 16 < a.Nout && y0 + wr * RW < a.Ho;
+    f4v acc[SL][RW];
+#pragma unroll
+    for (int s = 0; s < SL; ++s)
+#pragma unroll
+        for (int r = 0; r < RW; ++r) acc[s][r] = f4v{0.f, 0.f, 0.f, 0.f};
+
+    // 64 consecutive LDS units from the lanes' addresses: channel chunk ch of
+    // p (zeros where !ok or past C).  !C8: channel counts that are not
+    // multiples of 8 go 2 channels at a time.
+    // Only the first lim units are written.
+    auto dma = [&](uint4* dst, int lim, auto addr) __attribute__((always_inline)) {
+        const gptr z = as_global(&tc_zero);
+        const int lane = opaque(tid & 63);
+        gptr p;
+        int nc;
+        if (C8) {
+            if (lane < lim) {
+                addr(lane, p, nc);
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(nc > 0 ? p : z),
+                                                 (ldsptr)dst, 16, 0, 0);
+            }
+        } else {
+            for (int j = 0; j < 4; ++j) {
+                const int l = 16 * j + (lane >> 2), c = 2 * (lane & 3);
+                if (l < lim) {
+                    addr(l, p, nc);
+                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(c < nc ? p + c : z),
+                                                     (ldsptr)(dst + 16 * j), 4, 0, 0);
+                }
+            }
+        }
+    };
+    // slice k of group g (of part a while g < na) into buffer xd
+    auto load_x = [&](uint4* xd, int k, int g) __attribute__((always_inline)) {
+        const bool pa = g < a.na, ups = TWO && pa;
+        const int us = ups ? 1 : 0;
+        const int C = pa ? a.Ca : a.Cb, c0 = 32 * (pa ? g : g - a.na);
+        const gptr src = as_global(pa ? a.xa : a.xb);
+        const int sW = a.Wi >> us, sH = a.Hi >> us, sD = a.Di >> us;
+        const int bx = (S * x0 >> us) - 1, by = (S * y0 >> us) - 1, zi = (S * z0 - 1 + k) >> us;
+        const bool zok = (unsigned)zi < (unsigned)sD;
+        const size_t base = ((size_t)bn * sD + (zok ? zi : 0)) * ((size_t)sH * sW) * C;
+        const int w = ups ? T::UXP : T::XP, rw = ups ? T::div(T::UXP) : T::div(T::XP), nun = ups ? T::UXU : T::XU;
+#pragma unroll
+        for (int u = 0; u < T::NU; ++u) {
+            const int p0 = (u * (T::NT / 64) + wave) * 64;
+            if (p0 >= nun) break;
+            // voxel, channel offset and number of channels of unit p
+            auto unit = [&](int p, size_t& o, int& c, int& nc) __attribute__((always_inline)) {
+                const int v = p >> 2, vy = (int)(__umul24(v, rw) >> 16);
+                int vx = v - (int)__umul24(vy, w);
+                if (S == 2 && !ups) vx = vx < 17 ? 2 * vx : 2 * vx - 33;  // even columns, then odd ones
+                const int X = bx + vx, Y = by + vy;
+                c = c0 + 8 * ((p & 3) ^ ((v >> 1) & 3));
+                const bool ok = zok && (unsigned)X < (unsigned)sW && (unsigned)Y < (unsigned)sH;
+                o = base + (size_t)(unsigned)(Y * sW + X) * C;
+                nc = ok ? C - c : 0;
+            };
+            if constexpr (FROMDY) {
+                const int p = p0 + (tid & 63);
+                size_t o;
+                int c, nc;
+                unit(p, o, c, nc);
+                uint4 r = make_uint4(0u, 0u, 0u, 0u);
+                if (nc > 0) r = p_from_dy8(a.dy, a.y, a.slope, o, c, C);
+                if (p < nun) xd[p] = r;
+            } else {  // a buffer's last units: lanes past it stay out
+                dma(xd + p0, nun - p0, [&](int l, gptr& p, int& nc) __attribute__((always_inline)) {
+                    size_t o;
+                    int c;
+                    unit(p0 + l, o, c, nc);
+                    p = src + o + c;
+                });
+            }
+        }
+    };
+    // the wave's share of the 9 (dz, dy) fragments of its tile at x shift dx
+    auto load_w = [&](uint4* wd, int k, int g, int dx) __attribute__((always_inline)) {
+        const bool pa = g < a.na;
+        const int C = pa ? a.Ca : a.Cb, c0 = 32 * (pa ? g : g - a.na);
+#pragma unroll
+        for (int u = 0; u < (9 + WR - 1) / WR; ++u) {
+            const int f = u * WR + wr;
+            if (f >= 9 || !tc_used<S>(k, f / 3, nz)) continue;  // what no output slice needs is not fetched
+            const int tap = GRAD ? 26 - (f * 3 + dx) : f * 3 + dx;
+            dma(wd + (wn * 9 + f) * 64, 64, [&](int l, gptr& p, int& nc) __attribute__((always_inline)) {
+                const int li = l >> 2, n = n0 + wn * 16 + li, c = c0 + 8 * ((l & 3) ^ ((li >> 1) & 3));
+                nc = n < a.Nout ? C - c : 0;
+                p = as_global(a.w) + ((size_t)n * 27 + tap) * Cin + (pa ? 0 : a.Ca) + c;
+            });
+        }
+    };
+    // order of the x shifts: the gradient takes the centre first
+    auto shift = [](int i) { return GRAD ? i ^ (i < 2 ? 1 : 0) : i; };
+    auto arrive = [&]() __attribute__((always_inline)) {
+        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): the wave's loads to LDS
+        __syncthreads();
+    };
+
+    load_x(xs, 0, 0);
+    load_w(ws, 0, 0, shift(0));
+    arrive();
+    int par = 0, wpar = 0;
+    for (int k = 0; k < nk; ++k) {
+        for (int g = 0; g < a.ng; ++g) {
+            const bool last = g + 1 == a.ng, more = !last || k + 1 < nk;
+            const int kn = last ? k + 1 : k, gn = last ? 0 : g + 1;
+            const bool ups = TWO && g < a.na;
+            for (int di = 0; di < 3; ++di) {
+                const int dx = shift(di);
+                const uint4* const xb = xs + par * T::XB;
+                const uint4* const wb = ws + wpar * T::WB;
+                uint4 X[T::XR], w[9];
+                if (active) {
+                    const int lane = opaque(tid & 63), li = lane & 15, kg = lane >> 4;
+                    const int px = ups ? (S * li + dx + 1) >> 1 : S == 1 ? li + dx : (dx & 1) * 17 + li + (dx >> 1);
+                    const int r0 = S * RW * wr, v0 = px + (ups ? (r0 / 2) * T::UXP : r0 * T::XP);
+                    int at[4];  // rows r, r + 4, ... share the XOR pattern
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) at[e] = 4 * v0 + (kg ^ (((v0 >> 1) + e) & 3));
+#pragma unroll
+                    for (int r = 0; r < T::XR; ++r) {
+                        const int ur = (r + 1) >> 1;
+                        X[r] = ups ? xb[at[ur & 3] + ur * T::UXP * 4] : xb[at[r & 3] + r * T::XP * 4];
+                    }
+                    const uint4* const ww = wb + wn * 9 * 64 + li * 4 + (kg ^ ((li >> 1) & 3));
+#pragma unroll
+                    for (int f = 0; f < 9; ++f) w[f] = ww[f * 64];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                if (di < 2) load_w(ws + (wpar ^ 1) * T::WB, k, g, shift(di + 1));
+                else if (more) load_w(ws + (wpar ^ 1) * T::WB, kn, gn, shift(0));
+                if (di == 0 && more) load_x(xs + (par ^ 1) * T::XB, kn, gn);
+                __builtin_amdgcn_sched_barrier(0);
+                if (active) {
+#pragma unroll
+                    for (int dz = 0; dz < 3; ++dz) {
+                        if (tc_used<S>(k, dz, nz)) {
+#pragma unroll
+                            for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+                                for (int yo = 0; yo < RW; ++yo)
+                                    acc[tc_slot<S>(dz)][yo] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                        as_bf8(w[3 * dz + dy]), as_bf8(X[S * yo + dy]), acc[tc_slot<S>(dz)][yo], 0, 0, 0);
+                        }
+                    }
+                    if (di == 2 && last) tc_advance<S, RW, GRAD>(a, acc, k, bn, z0, y0 + wr * RW, x0, n0 + wn * 16);
+                }
+                wpar ^= 1;
+                arrive();
+            }
+            par ^= 1;
+        }
+    }
+}
+
+template <int S, int RW, int WR, int WN, int KIND, bool FROMDY, bool GRAD>
+hipError_t tc_launch(TcArgs& a, hipStream_t st)
+{
+    using T = TcTile<S, RW, WR, WN, KIND>;
+    a.na = (a.Ca + 31) / 32;
+    a.ng = a.na + (a.Cb + 31) / 32;
+    a.nfrag = tc_frags(tc_type(KIND, 0)) * a.na + tc_frags(tc_type(KIND, 1)) * (a.ng - a.na);
+    // steps alternate the two buffers: the two parts of TC_MIX have one each
+    const int ba = KIND == TC_FULL_UPS && T::buf(1) > T::buf(0) ? T::buf(1) : T::buf(0);
+    a.buf[0] = tc_resident(KIND) ? WN * a.nfrag * 64 : 0;
+    a.buf[1] = a.buf[0] + ba;
+    const int lds = (a.buf[1] + (KIND == TC_MIX ? T::buf(1) : ba)) * 16;
+    const hipError_t e = tc_plan(a, a.Do, a.Ho, a.Wo, T::YT, WN, tc_resident_blocks(lds, T::NT, RW));
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((conv_tile_kernel<S, RW, WR, WN, KIND, FROMDY, GRAD>), dim3((unsigned)a.nblocks), dim3(T::NT),
+                       lds, st, a);
+    return hipGetLastError();
+}
+
+template <int S, int RW, int WR, int WN, bool TWO, bool C8, bool FROMDY, bool GRAD>
+hipError_t wd_launch(TcArgs& a, hipStream_t st)
+{
+    using T = WdTile<S, RW, WR, WN>;
+    a.na = (a.Ca + 31) / 32;
+    a.ng = a.na + (a.Cb + 31) / 32;
+    const hipError_t e = tc_plan(a, a.Do, a.Ho, a.Wo, T::YT, WN, tc_resident_blocks(T::LDS, T::NT, RW));
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((conv_wide_kernel<S, RW, WR, WN, TWO, C8, FROMDY, GRAD>), dim3((unsigned)a.nblocks), dim3(T::NT),
+                       T::LDS, st, a);
+    return hipGetLastError();
+}
+
+// Tile shape by the number of 16-channel output tiles: a wave takes one, and
+// the waves that remain split rows, so that a block's weights and slices are
+// shared by as many waves as the layer allows.  4 is also the shape of wider
+// layers (several blocks per column).  Thin layers wait for memory, not for
+// the matrix cores: 4 rows per wave leave registers for twice the waves (16 ->
+// 4 channels, batch of 4: 0.54 -> 0.49 ms); with 3 tiles the gradient's
+// stores decide, and 8 rows are faster (16 -> 48: 1.68 against 1.93 ms).
+template <int S, int KIND, bool FROMDY, bool GRAD>
+hipError_t tc_shape(TcArgs& a, hipStream_t st)
+{
+    const int nt = (a.Nout + 15) / 16;
+    if constexpr (S == 1) {
+        if (nt == 1) return tc_launch<1, 4, 4, 1, KIND, FROMDY, GRAD>(a, st);
+        if (nt == 2) return tc_launch<1, 4, 2, 2, KIND, FROMDY, GRAD>(a, st);
+        if (nt % 3 == 0 && nt % 4 != 0) return tc_launch<1, 8, 1, 3, KIND, FROMDY, GRAD>(a, st);
+        return tc_launch<1, 4, 2, 4, KIND, FROMDY, GRAD>(a, st);
+    } else {
+        if (nt <= 2) return tc_launch<2, 2, 4, 2, KIND, FROMDY, GRAD>(a, st);
+        return tc_launch<2, 4, 2, 4, KIND, FROMDY, GRAD>(a, st);
+    }
+}
+
+template <int S, bool TWO, bool FROMDY, bool GRAD>
+hipError_t wd_shape(TcArgs& a, hipStream_t st)
+{
+    const int nt = (a.Nout + 15) / 16;
+    if ((a.Ca | a.Cb) & 7) return wd_launch<S, S == 1 ? 8 : 4, 2, 4, TWO, false, FROMDY, GRAD>(a, st);
+    if constexpr (S == 1) {
+        if (nt == 1) return wd_launch<1, 8, 4, 1, TWO, true, FROMDY, GRAD>(a, st);
+        if (nt == 2) return wd_launch<1, 8, 2, 2, TWO, true, FROMDY, GRAD>(a, st);
+        // 6 tiles: three blocks of 2 fill the four SIMDs evenly, two of 3 do not (32 -> 96 gradient: 0.73 against
+        // 1.02 ms)
+        if (nt == 6) return wd_launch<1, 8, 2, 2, TWO, true, FROMDY, GRAD>(a, st);
+        if (nt % 3 == 0 && nt % 4 != 0) return wd_launch<1, 8, 1, 3, TWO, true, FROMDY, GRAD>(a, st);
+        if (a.Ho > 8) return wd_launch<1, 8, 2, 4, TWO, true, FROMDY, GRAD>(a, st);
+        return wd_launch<1, 8, 1, 4, TWO, true, FROMDY, GRAD>(a, st);
+    } else {
+        // half the taps per input slice are too little work for a barrier per x shift: one step per group, weights
+        // through L2 (32 -> 64, batch of 4: 0.11 against 0.19 ms)
+        constexpr int KIND = TWO ? TC_FULL_UPS : TC_FULL;
+        if (nt <= 2) return tc_launch<2, 4, 2, 2, KIND, FROMDY, GRAD>(a, st);
+        return tc_launch<2, 8, 1, 4, KIND, FROMDY, GRAD>(a, st);
+    }
+}
+
+template <int S, bool FROMDY, bool GRAD>
+hipError_t tc_dispatch(TcArgs& a, bool ups, hipStream_t st)
+{
+    if constexpr (!GRAD) {
+        if (ups) {
+            if constexpr (S == 1)
+                if (a.Nout <= 16 && a.Ca % 8 == 0 && a.Cb % 8 == 0 && a.Ca <= 32 && a.Cb > 0 && a.Cb <= 16)
+                    return tc_launch<1, 8, 4, 1, TC_MIX, FROMDY, GRAD>(a, st);
+            return wd_shape<S, true, FROMDY, GRAD>(a, st);
+        }
+    }
+    if (a.Cb == 0 && a.Ca <= 8) return tc_shape<S, TC_QUARTER, FROMDY, GRAD>(a, st);
+    if (a.Cb == 0 && a.Ca <= 16) return tc_shape<S, TC_HALF, FROMDY, GRAD>(a, st);
+    return wd_shape<S, false, FROMDY, GRAD>(a, st);
+}
+
+}  // namespace
+
+hipError_t conv_fwd_launch(const ConvGeom& g, const unsigned short* xa, const unsigned short* xb,
+                           const unsigned short* w, const float* bias, int act, float slope, unsigned short* ybf,
+                           float* yf, hipStream_t st)
+{
+    TcArgs a{};
+    a.N = g.N; a.Di = g.Di; a.Hi = g.Hi; a.Wi = g.Wi; a.Do = g.Do; a.Ho = g.Ho; a.Wo = g.Wo;
+    a.Ca = g.Ca; a.Cb = g.Cb; a.Nout = g.Cout;
+    a.xa = xa; a.xb = xb; a.w = w; a.bias = bias; a.act = act; a.slope = slope; a.ybf = ybf; a.yf = yf;
+    const bool ups = g.ups != 0;
+    return g.stride == 1 ? tc_dispatch<1, false, false>(a, ups, st) : tc_dispatch<2, false, false>(a, ups, st);
+}
+
+hipError_t conv_dgrad1_launch(const ConvGeom& g, const float* dy, const unsigned short* y, float slope,
+                              const unsigned short* pb, const unsigned short* wt, float* dx, int accumulate,
+                              hipStream_t st)
+{
+    TcArgs a{};
+    a.N = g.N; a.Di = a.Do = g.Di; a.Hi = a.Ho = g.Hi; a.Wi = a.Wo = g.Wi;
+    a.Ca = g.Cout; a.Nout = g.Ca + g.Cb;
+    a.xa = pb; a.dy = dy; a.y = y; a.slope = slope; a.w = wt; a.yf = dx; a.accumulate = accumulate;
+    return pb ? tc_dispatch<1, false, true>(a, false, st) : tc_dispatch<1, true, true>(a, false, st);
+}
+
+}  // namespace ffdp

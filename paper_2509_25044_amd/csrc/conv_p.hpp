@@ -15,4 +15,12 @@ hipError_t act_grad_launch(const float* dy, const unsigned short* y, float slope
 hipError_t conv_bwd_data_p_launch(const ConvGeom& g, const unsigned short* p, const unsigned short* wt, float* dx,
                                   int accumulate, hipStream_t st);
 
+// input gradient of a stride-1 and of a stride-2 layer, from pb or (pb NULL) from dy and y
+hipError_t conv_dgrad1_launch(const ConvGeom& g, const float* dy, const unsigned short* y, float slope,
+                              const unsigned short* pb, const unsigned short* wt, float* dx, int accumulate,
+                              hipStream_t st);
+hipError_t conv_dgrad2_launch(const ConvGeom& g, const float* dy, const unsigned short* y, float slope,
+                              const unsigned short* pb, const unsigned short* wt, float* dx, int accumulate,
+                              hipStream_t st);
+
 }  // namespace ffdp

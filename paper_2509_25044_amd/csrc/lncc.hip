@@ -670,13 +670,15 @@ LnccLaunch lncc_plan(int D, int H, int W, int win, int mode)
     const long long tiles = (long long)L.ntx * L.nty;
     // z-chunks: blocks are dispatched as CUs free up, so the run ends after
     // ceil(nblocks / slots) block times of (zchunk + 2 R2) slices each (slots
-    // = resident blocks on 256 CUs).  Take the chunk count (z-chunks of at
-    // least 16 slices) that minimises that estimate; ties go to fewer chunks.
+    // = resident blocks on 256 CUs).  Take the chunk count that minimises
+    // that estimate; ties go to fewer chunks.  Small volumes end up with
+    // chunks of a slice or two: the halo slices are sampled again by CUs that
+    // would stand idle (40 x 48 x 56, w = 7: 148 -> 52 us against chunks of at
+    // least 16 slices).
     const long long slots = 256LL * (L.nt >= 1024 ? 1 : ((win <= 5) ? 2 : 1));
-    const int maxchunks = max(1, D / 16);
     long long best = -1;
     int bc = 1;
-    for (int c = 1; c <= maxchunks && c <= 64; ++c) {
+    for (int c = 1; c <= D && (c <= 64 || tiles * c <= slots); ++c) {
         const int zc = (D + c - 1) / c;
         const int nc = (D + zc - 1) / zc;
         const long long rounds = (tiles * nc + slots - 1) / slots;

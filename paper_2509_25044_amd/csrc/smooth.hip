@@ -167,10 +167,22 @@ static hipError_t smooth_dispatch(const float* in, float* out, int D, int H, int
 {
     const int ntx = (W + SM_TX - 1) / SM_TX, nty = (H + SM_TY - 1) / SM_TY;
     const int tiles = ntx * nty;
+    // About 2048 blocks in chunks of at least 32 slices; where that leaves the
+    // chip idle (small volumes), the chunk count with the fewest rounds of 1024
+    // resident blocks times the slices of a block, its 2R halo slices included
+    // (40 x 48 x 56: smoothed Adam step 40 -> 11 us, smoothing 19 -> 7 us).
     int chunks = (2048 + tiles * channels - 1) / (tiles * channels);
     const int maxchunks = (D + 31) / 32;
     if (chunks > maxchunks) chunks = maxchunks;
     if (chunks < 1) chunks = 1;
+    if ((long long)tiles * channels * chunks < 1024) {
+        long long best = -1;
+        for (int c = 1; c <= D && c <= 1024; ++c) {
+            const int zc = (D + c - 1) / c, n = (D + zc - 1) / zc;
+            const long long cost = ((long long)tiles * channels * n + 1023) / 1024 * (zc + 2 * R);
+            if (best < 0 || cost < best) { best = cost; chunks = n; }
+        }
+    }
     const int zchunk = (D + chunks - 1) / chunks;
     chunks = (D + zchunk - 1) / zchunk;
     dim3 grid(ntx, nty * chunks, channels), block(SM_NT);

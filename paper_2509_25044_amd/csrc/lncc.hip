@@ -30,18 +30,41 @@
 //    scatters F(zo) a - Mw(zo) c + e into the accumulators of the 2r+1
 //    pending output slices of the thread's column (the z-window), and the
 //    oldest one becomes grad_u with dMw/dp from the ring;
-//  * the x- and y-window passes read and write 2 floats per LDS access;
+//  * the x-window passes form 4 outputs of one channel from 16-byte LDS reads
+//    (of a, c, e with the terms common to the four summed once), stage C 2 per
+//    8-byte read;
 //  * statistics use values shifted by a per-block constant (F and M at the
 //    tile centre).  With padded voxels shifted too, A, B, C and the adjoint
 //    are unchanged in exact arithmetic and the fp32 cancellation in
 //    B = mu_FF - mu_F^2 shrinks;
 //  * window sums are direct w-term sums (no running add/subtract drift).
+//
+// Windows 7 and 9 with border padding run as two kernels where lncc_split
+// expects that to be faster: the same streaming kernel with a halo of r instead
+// of 2r in x and y (MODE_ACE; 512 threads, two blocks per CU) forms a, c, e,
+// sums them along z and leaves the three sums in grad_u, and lncc_xy_kernel
+// replaces them, slice by slice in place, by the gradient.  No workspace.
+#include "conv_types.hpp"
+#include <utility>
 #include "device.hpp"
 #include "internal.hpp"
 
 namespace ffdp {
 
-enum { MODE_FWD = 0, MODE_BWD = 1, MODE_ANTS = 2 };
+// MODE_ACE: the first half of the split adjoint (z-window sums of a, c, e into grad_u)
+enum { MODE_FWD = 0, MODE_BWD = 1, MODE_ANTS = 2, MODE_ACE = 3 };
+
+template <class F, int... I>
+__device__ __forceinline__ void static_for_impl(F& f, std::integer_sequence<int, I...>)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+// f(0), ..., f(N - 1) with the index a constant
+template <int N, class F>
+__device__ __forceinline__ void static_for(F f)
+{
+    static_for_impl(f, std::make_integer_sequence<int, N>{});
+}
 
 __host__ __device__ constexpr int round4(int v) { return (v + 3) & ~3; }
 
@@ -51,15 +74,16 @@ struct LnccTile {
     static constexpr int TX = TX_, TY = TY_, NT = TX_ * TY_;
     static constexpr int R2 = (MODE == MODE_BWD) ? 2 * r : r;  // stage-A halo
     static constexpr int R1 = (MODE == MODE_BWD) ? r : 0;      // stage-C halo
+    static constexpr int RZ = (MODE == MODE_BWD || MODE == MODE_ACE) ? 2 * r : r;  // slices beyond the chunk
     static constexpr int X2 = TX + 2 * R2, Y2 = TY + 2 * R2;
     static constexpr int X1 = TX + 2 * R1, Y1 = TY + 2 * R1;
     // One LDS row pitch for stage-A data and its x-windowed copy, so that the
-    // 2-wide runs of stages B and C map consecutive lanes to consecutive
-    // addresses (no bank conflicts where a wave crosses rows).  Runs past X1
-    // read the next row and produce values that are never used.
+    // 2-wide runs of stage C map consecutive lanes to consecutive addresses
+    // (no bank conflicts where a wave crosses rows).  Runs past X1 read the
+    // next row and produce values that are never used.
     static constexpr int X2p = round4(X2 > X1 + 2 * r ? X2 : X1 + 2 * r);
     static constexpr int X1p = X2p;
-    static constexpr int NV = (WIN + 2) / 2;         // float2 reads per 2-wide x-window run
+    static constexpr int NV = (WIN + 6) / 4;         // float4 reads per 4-wide x-window run
     static constexpr int NA = Y2 * X2p;              // floats per channel, stage A
     static constexpr int NB = Y2 * X1p;              // x-window
     static constexpr int NC = Y1 * X1p;              // a, c, e
@@ -68,17 +92,20 @@ struct LnccTile {
     static constexpr int PH = (NH + NT - 1) / NT;
     static constexpr int NW = NT / 64;               // waves per block
     static constexpr int QW = (NH + NW - 1) / NW;    // halo points per wave when PH == 1
-    static constexpr int RB = Y2 * X1p / 2;          // 2-wide runs, stage B
+    static constexpr int NRB = (X1 + 3) / 4;         // 4-wide runs of a row
+    static constexpr int RB = 5 * Y2 * NRB;          // stage B, one channel each
     static constexpr int RC = Y1 * X1p / 2;          // 2-wide runs, stage C (adjoint mode)
-    static constexpr int RD = Y1 * TX / 2;           // 2-wide runs, stage D
-    static constexpr int NG = (MODE != MODE_FWD) ? 3 * WIN * NT : 0;  // dMw/dp ring, thread-private
+    static constexpr int RD = 3 * Y1 * TX / 4;       // 4-wide runs, stage D, one channel each
+    static constexpr int NG = (MODE == MODE_BWD || MODE == MODE_ANTS) ? 3 * WIN * NT : 0;  // dMw/dp ring, thread-private
+    // split adjoint, w = 9: the z rings of a and c go to LDS (thread-private) so that two blocks' registers fit a CU
+    static constexpr int NAC = (MODE == MODE_ACE && WIN == 9) ? 2 : 0;
     // adjoint: the loss accumulator (one double per thread) also lives in LDS
     static constexpr int NL = (MODE == MODE_BWD) ? 2 * NT : 0;
     // LDS layout: the thread-private ring first, so that every slot is an
     // immediate offset (below 64 KB) from the thread's own address; then the
     // stage buffers and the loss doubles.
     static constexpr int OG = 0;
-    static constexpr int OA = OG + NG;                  // stage A  [5][Y2][X2p]
+    static constexpr int OA = OG + (MODE == MODE_ACE && WIN == 9 ? 2 * WIN * NT : NG);  // stage A  [5][Y2][X2p]
     static constexpr int OB = OA + 5 * NA;              // stage B  [5][Y2][X1p]
     static constexpr int OL = (OB + 5 * NB + 1) & ~1;   // loss doubles
     static constexpr int LDS_FLOATS = OL + NL;
@@ -87,25 +114,43 @@ struct LnccTile {
     static_assert(3 * NC <= 5 * NA && 3 * ND <= 5 * NB, "aliased LDS buffers must fit");
 };
 
-// 2-wide run of w-tap window sums along a row: out[e] = sum_{d<w} row[e + d]
-template <int WIN, int NV>
-__device__ __forceinline__ float2 xwin2(const float* row)
+// w-tap window sums of 4 consecutive positions, v[0 .. w + 2] -> o[e] = sum_{d<w} v[e + d]
+template <int WIN>
+__device__ __forceinline__ void win4(const float* v, float* o)
 {
-    float v[2 * NV];
-    const float2* src = reinterpret_cast<const float2*>(row);
+    float core = WIN > 3 ? v[3] : 0.0f;  // common to the four
+#pragma unroll
+    for (int d = 4; d < WIN; ++d) core += v[d];
+    const float lo = v[1] + v[2], hi = v[WIN] + v[WIN + 1];
+    o[0] = core + (v[0] + lo);
+    o[1] = core + (lo + v[WIN]);
+    o[2] = core + (v[2] + hi);
+    o[3] = core + (hi + v[WIN + 2]);
+}
+
+// 4-wide run along a row: 16-byte reads and one 16-byte write.  SHARED: win4.
+// The statistics' sums (SHARED false) are added in order instead: their means
+// cancel, up to w^3 fold where a window lies mostly in the padding.
+template <int WIN, int NV, bool SHARED>
+__device__ __forceinline__ void xwin4(const float* row, float* out)
+{
+    float v[4 * NV], o[4];
 #pragma unroll
     for (int n = 0; n < NV; ++n) {
-        const float2 t = src[n];
-        v[2 * n] = t.x;
-        v[2 * n + 1] = t.y;
+        const float4 t = reinterpret_cast<const float4*>(row)[n];
+        v[4 * n] = t.x; v[4 * n + 1] = t.y; v[4 * n + 2] = t.z; v[4 * n + 3] = t.w;
     }
-    float o0 = v[0], o1 = v[1];
+    if (SHARED) {
+        win4<WIN>(v, o);
+    } else {
 #pragma unroll
-    for (int d = 1; d < WIN; ++d) {
-        o0 += v[d];
-        o1 += v[d + 1];
+        for (int e = 0; e < 4; ++e) {
+            o[e] = v[e];
+#pragma unroll
+            for (int d = 1; d < WIN; ++d) o[e] += v[e + d];
+        }
     }
-    return make_float2(o0, o1);
+    *reinterpret_cast<float4*>(out) = make_float4(o[0], o[1], o[2], o[3]);
 }
 
 // Addressing.  LNCC_ADDR32: the whole volume lies within 4 GB of its base, so
@@ -141,6 +186,11 @@ __device__ __forceinline__ lncc_f2a ld2(const float* __restrict__ base, unsigned
 {
     if (ADDR == LNCC_ADDR64) return *reinterpret_cast<const lncc_f2a*>(base + idx);
     return *reinterpret_cast<const lncc_f2a*>(reinterpret_cast<const char*>(base) + idx * 4u);
+}
+
+__device__ __forceinline__ f32x4_a4 ld4(const float* __restrict__ base, unsigned idx)  // 32-bit byte offset
+{
+    return *reinterpret_cast<const f32x4_a4*>(reinterpret_cast<const char*>(base) + idx * 4u);
 }
 
 // grad_u is written once and not read again here: non-temporal stores
@@ -250,19 +300,47 @@ __device__ __forceinline__ Tri interp_pending(const Pend& g)
     return t;
 }
 
+// The value that the fields of the split adjoint are taken relative to: the
+// mean of 64 grid samples, the same in every block.  sum a (F - ref) - c (Mw -
+// ref) cancels less the nearer ref lies to the values (a mean does as well as
+// a value of the tile; a reference of 0 doubles the gradient's rounding
+// error).  Samples that are not finite are left out.
+__device__ __forceinline__ void lncc_reference(const float* __restrict__ F, const float* __restrict__ M, int D, int H,
+                                               int W, float& rf, float& rm)
+{
+    const int l = threadIdx.x & 63;
+    const int x = (int)((2ll * (l & 3) + 1) * W / 8), y = (int)((2ll * ((l >> 2) & 3) + 1) * H / 8);
+    const int z = (int)((2ll * (l >> 4) + 1) * D / 8);
+    const size_t i = ((size_t)z * H + y) * W + x;
+    rf = F[i];
+    rm = M[i];
+    const bool ok = fabsf(rf) < 1e30f && fabsf(rm) < 1e30f;
+    float n = ok ? 1.0f : 0.0f;
+    rf = ok ? rf : 0.0f;
+    rm = ok ? rm : 0.0f;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        rf += __shfl_xor(rf, o);
+        rm += __shfl_xor(rm, o);
+        n += __shfl_xor(n, o);
+    }
+    rf = n > 0.0f ? rf / n : 0.0f;
+    rm = n > 0.0f ? rm / n : 0.0f;
+}
+
 // Held to 128 VGPRs where 16 waves share a CU (1024-thread blocks, or two
 // 512-thread blocks for windows up to 5); a 768-thread block is held to 168
 // by its launch bound.  ADDR: see ld().
 template <int WIN, int MODE, int PAD, int ADDR, int TX_, int TY_>
 __global__ void __launch_bounds__(TX_ * TY_)
-    __attribute__((amdgpu_waves_per_eu((TX_ * TY_ >= 1024 || WIN <= 5) ? 4 : 2, 8)))
+    __attribute__((amdgpu_waves_per_eu((TX_ * TY_ >= 1024 || WIN <= 5 || MODE == MODE_ACE || MODE == MODE_FWD) ? 4 : 2, 8)))
 lncc_kernel(LnccArgs a)
 {
     using T = LnccTile<WIN, MODE, TX_, TY_>;
     constexpr int r = T::r, TX = T::TX, TY = T::TY, NT = T::NT;
-    constexpr int R2 = T::R2, R1 = T::R1, X2 = T::X2, X1 = T::X1;
+    constexpr int R2 = T::R2, R1 = T::R1, RZ = T::RZ, X2 = T::X2, X1 = T::X1;
     constexpr int X1p = T::X1p, X2p = T::X2p;
-    constexpr bool DER = (MODE != MODE_FWD);  // keep dMw/dp of the tile voxel
+    constexpr bool DER = (MODE == MODE_BWD || MODE == MODE_ANTS);  // keep dMw/dp of the tile voxel
     constexpr float inv = 1.0f / float(WIN * WIN * WIN);
     __shared__ __attribute__((aligned(16))) float lds[T::LDS_FLOATS];
     float* sA = lds + T::OA;                   // [5][Y2][X2p]  z-window sums
@@ -285,12 +363,12 @@ lncc_kernel(LnccArgs a)
     const int tid = threadIdx.x;
 
     // Window of the 32-bit addressing (ADDRWIN): zspan slices from zb, centred
-    // on the slices the block streams (z0 - R2 - 1 .. z1 + R2); the launcher
-    // guarantees zspan >= zchunk + 2 R2 + 4, so all of those lie inside.
+    // on the slices the block streams (z0 - RZ - 1 .. z1 + RZ); the launcher
+    // guarantees zspan >= zchunk + 2 RZ + 4, so all of those lie inside.
     int zb = 0;
     if (ADDR == LNCC_ADDRWIN) {
-        const int slack = a.zspan - (z1 - z0) - 2 * R2 - 4;
-        zb = min(max(z0 - R2 - 2 - slack / 2, 0), max(D - a.zspan, 0));
+        const int slack = a.zspan - (z1 - z0) - 2 * RZ - 4;
+        zb = min(max(z0 - RZ - 2 - slack / 2, 0), max(D - a.zspan, 0));
     }
     const size_t wb = (size_t)zb * HW;  // element offset of the window
     const float* __restrict__ F = a.F;
@@ -343,6 +421,18 @@ lncc_kernel(LnccArgs a)
     for (int q = 0; q < (MODE == MODE_BWD ? WIN : 1); ++q) zacc[q] = 0.f;
     double lsum = 0.0;
     if (MODE == MODE_BWD) sL[tid] = 0.0;
+    float rA[MODE == MODE_ACE ? 3 : 1][WIN];       // a, c, e of the tile voxel: last w slices
+    float refF = 0.f, refM = 0.f;
+    if (MODE == MODE_ACE) {
+        lncc_reference(F, M, D, H, W, refF, refM);
+        refF = sF - refF;
+        refM = sM - refM;
+#pragma unroll
+        for (int q = 0; q < 3 * WIN; ++q) {
+            if (q / WIN < T::NAC) sG[q * NT + tid] = 0.f;
+            else rA[MODE == MODE_ACE ? q / WIN : 0][q % WIN] = 0.f;
+        }
+    }
 
     // stage-A points of this thread: k = 0 the tile voxel, k >= 1 halo points
     constexpr int P = 1 + T::PH;
@@ -401,17 +491,20 @@ lncc_kernel(LnccArgs a)
     // start of stage A 3% slower.  The memory counter retires loads in
     // order, so where a load sits decides which waits it lengthens.)
     constexpr int KH = (MODE == MODE_BWD) ? 1 : P;  // points issued right after stage A
-    load_u(z0 - R2, 0, P);
-    issue(z0 - R2, 0, P);
-    load_u(z0 - R2 + 1, 0, KH);
+    load_u(z0 - RZ, 0, P);
+    issue(z0 - RZ, 0, P);
+    load_u(z0 - RZ + 1, 0, KH);
 
-    const int nsteps = (z1 - z0) + 2 * R2;
+    const int nsteps = (z1 - z0) + 2 * RZ;
     for (int base = 0; base < nsteps; base += WIN) {
-#pragma unroll
-        for (int j = 0; j < WIN; ++j) {
+        // the ring slot j is a constant of each copy (a loop of 9 with an exit is
+        // not unrolled, and ring accesses become selects: w = 9 at 160 x 192 x 224,
+        // forward 123 -> 89 us, adjoint 382 -> 286 us)
+        static_for<WIN>([&](auto jc) __attribute__((always_inline)) {
+            constexpr int j = decltype(jc)::value;
             const int s = base + j;
-            if (s >= nsteps) break;
-            const int zi = z0 - R2 + s;  // slice entering the rings
+            if (s >= nsteps) return;
+            const int zi = z0 - RZ + s;  // slice entering the rings
             const bool zin = (zi >= 0) && (zi < D);
             // ---- stage A: sample, push into the rings, z-window sums ----
             // Raised wave priority while the gathers of this slice are
@@ -476,16 +569,13 @@ lncc_kernel(LnccArgs a)
                     load_u(zi + 1, KH, P);
                     issue(zi + 1, KH, P);
                 }
-                continue;
+                return;
             }
             __syncthreads();
             // ---- stage B: x-window, 2 outputs per thread ----
             for (int q = tid; q < T::RB; q += NT) {
-                const int ly = q / (X1p / 2), lx0 = 2 * (q - ly * (X1p / 2));
-#pragma unroll
-                for (int c = 0; c < 5; ++c)
-                    *reinterpret_cast<float2*>(sB + c * T::NB + ly * X1p + lx0) =
-                        xwin2<WIN, T::NV>(sA + c * T::NA + ly * X2p + lx0);
+                const int row = q / T::NRB, lx0 = 4 * (q - row * T::NRB);  // rows of all channels
+                xwin4<WIN, T::NV, false>(sA + row * X2p + lx0, sB + row * X1p + lx0);
             }
             __syncthreads();
             // ---- stage C: y-window, statistics, loss term, adjoint fields ----
@@ -561,6 +651,35 @@ lncc_kernel(LnccArgs a)
                 const float C = fmaf(-mm, mm, S[3] * inv);
                 const float rD = __builtin_amdgcn_rcpf(fmaf(B, C, eps));  // 1 ulp reciprocal
                 if (inroi && zown) lsum += (double)(A * A * rD);
+                if constexpr (MODE == MODE_ACE) {
+                    const float ac = inroi ? 2.0f * gi * A * rD : 0.0f;
+                    const float cc = ac * A * B * rD;
+                    if (T::NAC) {
+                        sG[j * NT + tid] = ac;
+                        sG[(WIN + j) * NT + tid] = cc;
+                    } else {
+                        rA[0][j] = ac;
+                        rA[1][j] = cc;
+                    }
+                    rA[2][j] = inroi ? fmaf(cc, mm + refM, -ac * (mf + refF)) : 0.0f;
+                    const int zo = zc - r;
+                    if (s >= 4 * r && gx < W && gy < H) {  // read again by the second half: plain stores
+                        float w0 = 0.f, w1 = 0.f, w2 = 0.f;
+#pragma unroll
+                        for (int q = 0; q < WIN; ++q) {
+                            if (!T::NAC) { w0 += rA[0][q]; w1 += rA[1][q]; }
+                            w2 += rA[2][q];
+                        }
+                        if (T::NAC) {
+#pragma unroll
+                            for (int q = 0; q < WIN; ++q) { w0 += sG[q * NT + tid]; w1 += sG[(WIN + q) * NT + tid]; }
+                        }
+                        const unsigned idx = imul<ADDR>(zo - zb, HW) + imul<ADDR>(gy, W) + gx;
+                        G0[idx] = w0;
+                        G1[idx] = w1;
+                        G2[idx] = w2;
+                    }
+                }
                 if (MODE == MODE_ANTS && zown && gx < W && gy < H) {
                     // gradient without the second window sum, at the voxel itself
                     const int sl = (j + WIN - r) % WIN;  // ring slot of slice zc
@@ -579,16 +698,13 @@ lncc_kernel(LnccArgs a)
                     st<ADDR>(G2, idx, g2);
                 }
             }
-            if (MODE != MODE_BWD) continue;
+            if (MODE != MODE_BWD) return;
             __syncthreads();
             load_u(zi + 1, KH, P);
             // ---- stage D: x-window of a, c, e ----
             for (int q = tid; q < T::RD; q += NT) {
-                const int ly = q / (TX / 2), lx0 = 2 * (q - ly * (TX / 2));
-#pragma unroll
-                for (int c = 0; c < 3; ++c)
-                    *reinterpret_cast<float2*>(sD + c * T::ND + ly * TX + lx0) =
-                        xwin2<WIN, T::NV>(sC + c * T::NC + ly * X1p + lx0);
+                const int row = q / (TX / 4), lx0 = 4 * (q - row * (TX / 4));
+                xwin4<WIN, T::NV, true>(sC + row * X1p + lx0, sD + row * TX + lx0);
             }
             __syncthreads();
             // ---- stages E/F: y-window, z-window by scatter, gradient ----
@@ -621,13 +737,161 @@ lncc_kernel(LnccArgs a)
             }
             issue(zi + 1, KH, P);
             load_u(zi + 2, 0, KH);
-        }
+        });
     }
     // ---- block loss partial (fixed-order tree) ----
     __syncthreads();
     if (MODE == MODE_BWD) lsum = sL[tid];
     double tot = block_sum<NT>(lsum, reinterpret_cast<double*>(lds));
     if (tid == 0) a.partial[blockIdx.x] = tot;
+}
+
+// Second half of the split adjoint: grad_u holds the z-window sums of a, c, e.
+// A block owns one z slice of all three channels and replaces them in place by
+// the gradient: it streams rows in y, and a row is overwritten only after the
+// rows it feeds have been read.  Rows go by chunks of RB.  Per step the next
+// chunk, loaded a step ahead, is laid into LDS; a thread forms the x-windows of
+// 4 columns of one of its rows into a ring of two chunks; then it takes 4 rows
+// of one column: y-windows, the sampler's derivative from gathers issued at
+// the start of the step (u a step ahead), gradient.  The block after the last
+// slice reduces the loss partials (as lncc_finalize).
+template <int WIN, int RB, int NT>
+__global__ void __launch_bounds__(NT) lncc_xy_kernel(LnccArgs a, int npart, double inv_nroi, float* loss)
+{
+    constexpr int r = (WIN - 1) / 2, NV = WIN + 3;
+    constexpr float inv = 1.0f / float(WIN * WIN * WIN);
+    static_assert(2 * r <= RB && r <= 4 && RB % 4 == 0, "a window spans two chunks of rows, a run three float4");
+    extern __shared__ float xf[];  // [3 fields][2 chunks][RB][PW], then the chunk laid in [3][RB][PW + 8]
+    const int tid = threadIdx.x;
+    const int D = a.D, H = a.H, W = a.W, HW = H * W;
+    const int z = xcd_remap(blockIdx.x, gridDim.x);
+    if (z == D) {
+        double s = 0.0;
+        for (int i = tid; i < npart; i += NT) s += a.partial[i];
+        s = block_sum<NT>(s, reinterpret_cast<double*>(xf));
+        if (tid == 0) *loss = (float)(1.0 - s * inv_nroi);
+        return;
+    }
+    float refF, refM;
+    lncc_reference(a.F, a.M, D, H, W, refF, refM);
+    const size_t N = (size_t)D * HW;
+    const int NR = (W + 3) >> 2, PW = 4 * NR, FS = 2 * RB * PW, RS = RB * (PW + 8);
+    float* const raw = xf + 3 * FS;
+    float* const G[3] = {a.gu, a.gu + N, a.gu + 2 * N};
+    const unsigned zoff = (unsigned)z * (unsigned)HW;
+
+    // the thread's run of 4 columns in the x pass (row xrow of a chunk) and its
+    // 4 rows of a column in the y pass; the launcher has one of each per thread
+    const int xrow = tid / NR, xrun = tid - xrow * NR, ygrp = tid / W, x = tid - ygrp * W;
+    const bool xact = xrow < RB, yact = ygrp < RB / 4;
+
+    // the rows [RB (c - 1) + r, RB c + r) are chunk c
+    f32x4_a4 v[3];
+    auto load_rows = [&](int c) {
+        const int y = RB * (c - 1) + r + xrow, cx = 4 * xrun;
+        const bool in = xact && y >= 0 && y < H;
+        const unsigned row = zoff + __umul24((unsigned)min(max(y, 0), H - 1), (unsigned)W);
+#pragma unroll
+        for (int f = 0; f < 3; ++f) {
+            f32x4_a4 t = {0.f, 0.f, 0.f, 0.f};
+            if (in && cx + 3 < W) {
+                t = ld4(G[f], row + cx);
+            } else if (in) {  // the row's last columns
+                if (cx < W) t.x = ld<LNCC_ADDR32>(G[f], row + cx);
+                if (cx + 1 < W) t.y = ld<LNCC_ADDR32>(G[f], row + cx + 1);
+                if (cx + 2 < W) t.z = ld<LNCC_ADDR32>(G[f], row + cx + 2);
+            }
+            v[f] = t;
+        }
+    };
+    float* const rawp = raw + xrow * (PW + 8) + 4 * xrun;
+    auto lay = [&]() {
+        if (!xact) return;
+#pragma unroll
+        for (int f = 0; f < 3; ++f) *reinterpret_cast<float4*>(rawp + f * RS + 4) = make_float4(v[f].x, v[f].y, v[f].z, v[f].w);
+    };
+    auto xpass = [&](int c) {
+        if (!xact) return;
+        float* const dst = xf + ((c & 1) * RB + xrow) * PW + 4 * xrun;
+#pragma unroll
+        for (int f = 0; f < 3; ++f) {
+            float t[12], o[4];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const float4 q = reinterpret_cast<const float4*>(rawp + f * RS)[k];
+                t[4 * k] = q.x; t[4 * k + 1] = q.y; t[4 * k + 2] = q.z; t[4 * k + 3] = q.w;
+            }
+            win4<WIN>(t + 4 - r, o);
+            *reinterpret_cast<float4*>(dst + f * FS) = make_float4(o[0], o[1], o[2], o[3]);
+        }
+    };
+    for (int q = tid; q < 3 * RB * 8; q += NT)  // the 4 columns left and right of the rows stay zero
+        raw[(q >> 3) * (PW + 8) + ((q & 4) ? PW + 4 : 0) + (q & 3)] = 0.f;
+    float un[4][3];  // u of the next step (rows clamped into the slice)
+    auto load_u = [&](int i) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const unsigned id = zoff + __umul24((unsigned)min(RB * i + 4 * ygrp + e, H - 1), (unsigned)W) + x;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) un[e][k] = a.u ? ld<LNCC_ADDR32>(a.u + k * N, id) : 0.f;
+        }
+    };
+    load_rows(0);
+    if (yact) load_u(0);
+    lay();
+    load_rows(1);
+    __syncthreads();
+    xpass(0);
+    __syncthreads();
+    const int nstep = (H + RB - 1) / RB;
+    for (int i = 0; i < nstep; ++i) {
+        const int y0 = RB * i + 4 * ygrp;
+        Pend g[4];
+        lay();
+        if (yact) {  // gathers of this step, u and rows of the next, in flight during the x pass
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int y = min(y0 + e, H - 1);
+                issue_point<PAD_BORDER, LNCC_ADDR32>(g[e], a.M, a.M, a.F, D, H, W, HW, 0, D, x, y, z,
+                                                     zoff + __umul24((unsigned)y, (unsigned)W) + x, un[e][0], un[e][1],
+                                                     un[e][2]);
+            }
+            load_u(min(i + 1, nstep - 1));
+        }
+        load_rows(i + 2);
+        __syncthreads();
+        xpass(i + 1);
+        __syncthreads();
+        if (yact && y0 < H) {
+            // y-windows of 4 rows; the first row used is RB - 2r + 4 ygrp rows into chunk i
+            const int b0 = (i & 1) * RB * PW, b1 = (1 - (i & 1)) * RB * PW - RB * PW;
+            float A[3][4], v[NV];
+            int at[NV];
+#pragma unroll
+            for (int n = 0; n < NV; ++n) {
+                const int L = RB - 2 * r + 4 * ygrp + n;
+                at[n] = L * PW + x + (L < RB ? b0 : b1);
+            }
+#pragma unroll
+            for (int f = 0; f < 3; ++f) {
+#pragma unroll
+                for (int n = 0; n < NV; ++n) v[n] = xf[f * FS + at[n]];
+                win4<WIN>(v, A[f]);
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int y = y0 + e;
+                const Tri t = interp_pending<true>(g[e]);
+                const float gm = fmaf(g[e].f - refF, A[0][e], fmaf(refM - t.v, A[1][e], A[2][e])) * inv;
+                if (y < H) {
+                    const unsigned id = zoff + __umul24((unsigned)y, (unsigned)W) + x;
+                    st<LNCC_ADDR32>(G[0], id, gm * t.dx);
+                    st<LNCC_ADDR32>(G[1], id, gm * t.dy);
+                    st<LNCC_ADDR32>(G[2], id, gm * t.dz);
+                }
+            }
+        }
+    }
 }
 
 // loss = 1 - sum(partials) / N_roi, summed in a fixed order
@@ -650,7 +914,8 @@ __global__ void __launch_bounds__(256) lncc_finalize(const double* __restrict__ 
 // output (its 4r halo) and its 167 VGPRs and 96 KB of LDS leave one block of
 // 8 waves per CU; 24 rows sample 2.06 points per output, and one block of
 // 12 waves fits (168 VGPRs, 134 KB): 512^3 adjoint 5.10 -> 4.74 ms, 1040^3
-// 45.6 -> 38.2 ms.  (32 x 32 does not fit the LDS; at w = 5 the two-block
+// 45.6 -> 38.2 ms (4.22 ms now; where lncc_split says so two kernels take its
+// place).  (32 x 32 does not fit the LDS; at w = 5 the two-block
 // 32 x 16 layout stays faster than any one-block tile.)
 static void lncc_tile(int win, int mode, int& tx, int& ty)
 {
@@ -664,25 +929,25 @@ LnccLaunch lncc_plan(int D, int H, int W, int win, int mode)
     lncc_tile(win, mode, L.tx, L.ty);
     L.nt = L.tx * L.ty;
     const int r = (win - 1) / 2;
-    const int R2 = (mode == MODE_BWD) ? 2 * r : r;
+    const int RZ = (mode == MODE_BWD || mode == MODE_ACE) ? 2 * r : r;
     L.ntx = (W + L.tx - 1) / L.tx;
     L.nty = (H + L.ty - 1) / L.ty;
     const long long tiles = (long long)L.ntx * L.nty;
     // z-chunks: blocks are dispatched as CUs free up, so the run ends after
-    // ceil(nblocks / slots) block times of (zchunk + 2 R2) slices each (slots
+    // ceil(nblocks / slots) block times of (zchunk + 2 RZ) slices each (slots
     // = resident blocks on 256 CUs).  Take the chunk count that minimises
     // that estimate; ties go to fewer chunks.  Small volumes end up with
     // chunks of a slice or two: the halo slices are sampled again by CUs that
     // would stand idle (40 x 48 x 56, w = 7: 148 -> 52 us against chunks of at
     // least 16 slices).
-    const long long slots = 256LL * (L.nt >= 1024 ? 1 : ((win <= 5) ? 2 : 1));
+    const long long slots = 256LL * (L.nt >= 1024 ? 1 : ((win <= 5 || mode == MODE_ACE || mode == MODE_FWD) ? 2 : 1));
     long long best = -1;
     int bc = 1;
     for (int c = 1; c <= D && (c <= 64 || tiles * c <= slots); ++c) {
         const int zc = (D + c - 1) / c;
         const int nc = (D + zc - 1) / zc;
         const long long rounds = (tiles * nc + slots - 1) / slots;
-        const long long cost = rounds * (zc + 2 * R2);
+        const long long cost = rounds * (zc + 2 * RZ);
         if (best < 0 || cost < best) { best = cost; bc = c; }
     }
     L.zchunk = (D + bc - 1) / bc;
@@ -696,15 +961,44 @@ LnccLaunch lncc_plan(int D, int H, int W, int win, int mode)
     const long long span = 4294967295LL / (4 * HW);  // whole slices within 4 GB of a base
     L.zspan = (int)min(span, (long long)D);
     if (W >= 2 && fit24 && N * 4 <= 4294967295LL) L.addr = LNCC_ADDR32;
-    else if (W >= 2 && fit24 && span >= L.zchunk + 2 * R2 + 4) L.addr = LNCC_ADDRWIN;
+    else if (W >= 2 && fit24 && span >= L.zchunk + 2 * RZ + 4) L.addr = LNCC_ADDRWIN;
     else L.addr = LNCC_ADDR64;  // also width-1 volumes (no x pairs)
     return L;
+}
+
+// Rows per step and threads of lncc_xy_kernel: one run of 4 columns and one of 4
+// rows per thread, and 3 RB (3 W + 8) floats of LDS.  W <= LNCC_XY_MAX_W.
+constexpr int LNCC_XY_MAX_W = 512;
+static int xy_rows(int W) { return W <= 256 ? 16 : 8; }
+
+// Does the adjoint of this shape run as two kernels (MODE_ACE, lncc_xy_kernel)?
+// Windows 7 and 9, whose fused kernel samples 2 and 3 points per output and
+// holds one block per CU; the second kernel's slices must fit LDS and 32-bit
+// offsets.  Then by an estimate of both, in us, from measured times of a
+// block's slice and step: the fused kernel takes 4.6 (w = 7) or 4.1 (w = 9) per
+// slice, the first half 3.7 or 4.3 with two blocks on a CU and about 2.2 with
+// one, the second 1.5 per step and 1.4 per 1000 voxels of it, twice that beyond
+// the last-level cache.  So few slices, with long second halves on few CUs, stay
+// fused (64 x 300 x 70, w = 7: 99 against 131 us), others split (160 x 192 x
+// 224: w = 7 187 against 236, w = 9 254 against 286; 40 x 48 x 56, w = 7: 36
+// against 50).  Windows 3 and 5 are faster fused everywhere but on toy sizes.
+static bool lncc_split(int D, int H, int W, int win, int pad)
+{
+    if (win < 7 || pad != PAD_BORDER || W > LNCC_XY_MAX_W) return false;
+    const LnccLaunch S = lncc_plan(D, H, W, win, MODE_ACE), B = lncc_plan(D, H, W, win, MODE_BWD);
+    if (S.addr != LNCC_ADDR32) return false;
+    const int halo = 2 * (win - 1), RB = xy_rows(W);
+    const double fused = (win == 7 ? 4.6 : 4.1) * ((B.nblocks + 255) / 256) * (B.zchunk + halo);
+    const double first = (S.nblocks <= 256 ? 2.2 : win == 7 ? 3.7 : 4.3) * ((S.nblocks + 511) / 512) * (S.zchunk + halo);
+    const double step = (1.5 + 0.0014 * RB * W) * ((double)D * H * W > 6.4e7 ? 2.0 : 1.0);
+    const double second = step * ((D + 255) / 256) * ((H + RB - 1) / RB);
+    return first + second < fused;
 }
 
 int lncc_max_blocks(int D, int H, int W, int win)
 {
     int n = 0;
-    for (int mode = 0; mode < 3; ++mode) n = max(n, lncc_plan(D, H, W, win, mode).nblocks);
+    for (int mode = 0; mode < 4; ++mode) n = max(n, lncc_plan(D, H, W, win, mode).nblocks);
     return n;
 }
 
@@ -749,10 +1043,38 @@ static hipError_t launch_mode(int win, int pad, const LnccLaunch& L, const LnccA
     }
 }
 
+template <int WIN, int RB, int NT>
+static hipError_t launch_xy(const LnccArgs& a, float* loss, double nroi, hipStream_t st)
+{
+    const int PW = (a.W + 3) & ~3, lds = 3 * RB * (3 * PW + 8) * (int)sizeof(float);
+    hipLaunchKernelGGL((lncc_xy_kernel<WIN, RB, NT>), dim3(a.D + (loss ? 1 : 0)), dim3(NT),
+                       max(lds, NT * (int)sizeof(double)), st, a, a.nblocks, 1.0 / nroi, loss);
+    return hipGetLastError();
+}
+
+template <int WIN>
+static hipError_t launch_split(const LnccArgs& a, float* loss, double nroi, hipStream_t st)
+{
+    hipLaunchKernelGGL((lncc_kernel<WIN, MODE_ACE, PAD_BORDER, LNCC_ADDR32, 32, 16>), dim3(a.nblocks), dim3(512), 0, st,
+                       a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    if (a.W <= 64) return launch_xy<WIN, 16, 256>(a, loss, nroi, st);  // 4 W threads, xy_rows(W) rows
+    if (a.W <= 128) return launch_xy<WIN, 16, 512>(a, loss, nroi, st);
+    if (a.W <= 256) return launch_xy<WIN, 16, 1024>(a, loss, nroi, st);
+    return launch_xy<WIN, 8, 1024>(a, loss, nroi, st);
+}
+
 hipError_t lncc_launch(int mode, int win, int pad, const LnccLaunch& L, const LnccArgs& a, float* loss, double nroi,
                        hipStream_t st)
 {
     hipError_t e;
+    if (mode == MODE_BWD && lncc_split(a.D, a.H, a.W, win, pad)) {
+        const LnccLaunch S = lncc_plan(a.D, a.H, a.W, win, MODE_ACE);
+        LnccArgs b = a;
+        b.ntx = S.ntx; b.nty = S.nty; b.zchunk = S.zchunk; b.nblocks = S.nblocks; b.zspan = S.zspan;
+        return win == 7 ? launch_split<7>(b, loss, nroi, st) : launch_split<9>(b, loss, nroi, st);
+    }
     if (mode == MODE_FWD) e = launch_mode<MODE_FWD>(win, pad, L, a, st);
     else if (mode == MODE_BWD) e = launch_mode<MODE_BWD>(win, pad, L, a, st);
     else e = launch_mode<MODE_ANTS>(win, pad, L, a, st);

@@ -82,6 +82,7 @@ hipError_t affine_reduce_launch(const double* part, int nblocks, double* out, hi
 // MI
 constexpr int MI_MAX_BINS = 256;
 constexpr int MI_LDS_TABLE_BINS = 128;  // log tables up to 128^2 floats (64 KB) are staged in LDS
+constexpr int MI_LDS_HIST = 160000;     // bytes of LDS a histogram may take
 constexpr int MI_TX = 64;
 constexpr int MI_TY = 4;
 constexpr int MI_NT = MI_TX * MI_TY;
@@ -100,6 +101,7 @@ struct MiArgs {
     int bins;
     int ntx, nty, zchunk, nblocks;
     int ncopy;       // LDS histogram copies, a power of two (set by mi_fwd_launch)
+    int rows, ngroups;  // F bins of an LDS histogram, and groups of them (set by mi_fwd_launch)
     int affine;      // 1: composite sampler with aff
     Affine aff;
     double* apart;   // [nblocks][12] partial dL/dA, dL/dt (affine adjoint)

@@ -269,14 +269,15 @@ struct ColumnSampler {
 // reaches column B + 4), odd.
 __host__ __device__ constexpr int mi_hist_pitch(int B) { return (B + 5) | 1; }
 
-// GLOB: the histogram is too large for LDS (a.ncopy == 0) and the taps are
-// added straight into the global one; otherwise into a.ncopy LDS copies.
-// (Compile-time, so that each atomic is an LDS or a global one, never flat.)
-template <bool HARD, int PAD, bool AFF, bool GLOB>
-__global__ void __launch_bounds__(MI_NT) mi_hist_kernel(MiArgs a, unsigned long long* __restrict__ ghist,
-                                                        unsigned long long* __restrict__ gflag)
+// TYB: rows of 64 threads in a block.  GRP: the histogram of all F bins does
+// not fit LDS; a block holds a.rows of them (group gi of a.ngroups) and leaves
+// the taps of the others to the blocks of their groups, which sample the same
+// voxels.
+template <bool HARD, int PAD, bool AFF, int TYB, bool GRP>
+__global__ void __launch_bounds__(MI_TX * TYB) mi_hist_kernel(MiArgs a, unsigned long long* __restrict__ ghist,
+                                                              unsigned long long* __restrict__ gflag)
 {
-    // LDS: a.ncopy copies of B rows (F bins, clamped) of mi_hist_pitch(B)
+    // LDS: a.ncopy copies of a.rows rows (F bins, clamped) of mi_hist_pitch(B)
     // >= B + 5 columns holding the Mw bins -2 .. B + 1 unclamped (column c at
     // c + 2), so the four columns of a patch are consecutive and each row of
     // the flush is one address plus immediate offsets; the clamp of those
@@ -284,20 +285,23 @@ __global__ void __launch_bounds__(MI_NT) mi_hist_kernel(MiArgs a, unsigned long 
     // up.  The pitch is odd: with an even one (a row is twice as many banks
     // wide) the same column of any two rows falls in one LDS bank, which is
     // what lanes with equal Mw bins and different F bins hit.  Copy stride
-    // B pitch + 1.  GLOB: the global [B][B] histogram, columns clamped.
+    // rows pitch + 1.
     extern __shared__ unsigned long long hist[];
-    const int B = a.bins, BB = B * B;
-    const int RP = GLOB ? B : mi_hist_pitch(B), CS = B * RP + 1;  // row pitch, copy stride
-    for (int q = threadIdx.x; !GLOB && q < a.ncopy * CS; q += MI_NT) hist[q] = 0ull;
-    unsigned long long* const mine = GLOB ? ghist : hist + (threadIdx.x & (a.ncopy - 1)) * CS;
+    constexpr int NT = MI_TX * TYB;
+    const int B = a.bins;
+    const int RP = mi_hist_pitch(B), CS = a.rows * RP + 1;  // row pitch, copy stride
+    for (int q = threadIdx.x; q < a.ncopy * CS; q += NT) hist[q] = 0ull;
+    unsigned long long* const mine = hist + (threadIdx.x & (a.ncopy - 1)) * CS;
     __shared__ int nanflag;
     if (threadIdx.x == 0) nanflag = 0;
     __syncthreads();
 
-    const int bid = xcd_remap(blockIdx.x, a.nblocks);
+    int bid = xcd_remap(blockIdx.x, a.nblocks);
+    const int r0 = GRP ? (bid % a.ngroups) * a.rows : 0;  // groups of one chunk side by side
+    if (GRP) bid /= a.ngroups;
     const int tx = bid % a.ntx, rest = bid / a.ntx, ty = rest % a.nty, ch = rest / a.nty;
     const int x = a.roi[4] + tx * MI_TX + (threadIdx.x % MI_TX);
-    const int y = a.roi[2] + ty * MI_TY + (threadIdx.x / MI_TX);
+    const int y = a.roi[2] + ty * TYB + (threadIdx.x / MI_TX);
     const int zb = a.roi[0] + ch * a.zchunk;
     const int ze = min(a.roi[1], zb + a.zchunk);
     const int H = a.H, W = a.W, HW = H * W;
@@ -311,25 +315,13 @@ __global__ void __launch_bounds__(MI_NT) mi_hist_kernel(MiArgs a, unsigned long 
     bool bad = false;
 
     auto flush = [&]() {
-        if (GLOB) {
-            int row[4], col[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                row[i] = (int)__umul24((unsigned)fold(cm + i, B), (unsigned)RP);
-                col[i] = fold(cn + i, B);
-            }
+        for (int i = 0; i < 4; ++i) {
+            const int m = fold(cm + i, B) - r0;
+            if (GRP && (unsigned)m >= (unsigned)a.rows) continue;
+            unsigned long long* rp = mine + (int)__umul24((unsigned)m, (unsigned)RP) + (cn + 2);
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int jj = 0; jj < 4; ++jj)
-                    atomicAdd(&mine[row[i] + col[jj]], to_fix(acc[i * 4 + jj]));  // unconditional: no branch per tap
-        } else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                unsigned long long* rp = mine + (int)__umul24((unsigned)fold(cm + i, B), (unsigned)RP) + (cn + 2);
-#pragma unroll
-                for (int jj = 0; jj < 4; ++jj) atomicAdd(rp + jj, to_fix(acc[i * 4 + jj]));
-            }
+            for (int jj = 0; jj < 4; ++jj) atomicAdd(rp + jj, to_fix(acc[i * 4 + jj]));
         }
     };
 
@@ -364,14 +356,14 @@ __global__ void __launch_bounds__(MI_NT) mi_hist_kernel(MiArgs a, unsigned long 
     }
     if (bad) nanflag = 1;
     __syncthreads();
-    for (int q = threadIdx.x; !GLOB && q < BB; q += MI_NT) {
+    for (int q = threadIdx.x; q < min(a.rows, B - r0) * B; q += NT) {
         const int r = q / B, c = q - r * B;
         // stored columns of bin c: c + 2, and the clamped ones beside the edges
         const int s0 = c == 0 ? 0 : c + 2, s1 = c == B - 1 ? B + 3 : c + 2;
         unsigned long long v = 0ull;
         for (int k = 0; k < a.ncopy; ++k)
             for (int sc = s0; sc <= s1; ++sc) v += hist[k * CS + r * RP + sc];
-        if (v) atomicAdd(&ghist[q], v);
+        if (v) atomicAdd(&ghist[r0 * B + q], v);
     }
     if (threadIdx.x == 0 && nanflag) atomicOr(gflag, 1ull);
 }
@@ -542,7 +534,7 @@ __global__ void __launch_bounds__(1024) mi_finalize(const unsigned long long* __
     __shared__ double pF[MI_MAX_BINS], pM[MI_MAX_BINS];
     __shared__ unsigned long long rowsum[MI_MAX_BINS];
     __shared__ unsigned long long colsum[MI_MAX_BINS], total_s;
-    __shared__ double logM[MI_MAX_BINS];
+    __shared__ double logF[MI_MAX_BINS], logM[MI_MAX_BINS];
     __shared__ double red[1024];
     const int BB = B * B, tid = threadIdx.x;
     // Integer row and column sums, in any order: 16 lanes to a row; to a column
@@ -571,9 +563,9 @@ __global__ void __launch_bounds__(1024) mi_finalize(const unsigned long long* __
     const double sc = total ? 1.0 / (double)total : 0.0;
     if (tid < B) {
         pF[tid] = (double)rowsum[tid] * sc;
-        const double pm = (double)colsum[tid] * sc;
-        pM[tid] = pm;
-        logM[tid] = pm > 0.0 ? log(pm) : 0.0;  // read only where p > 0
+        pM[tid] = (double)colsum[tid] * sc;
+        logF[tid] = pF[tid] > 0.0 ? log(pF[tid]) : 0.0;  // read only where p > 0
+        logM[tid] = pM[tid] > 0.0 ? log(pM[tid]) : 0.0;
     }
     __syncthreads();
     double part = 0.0;
@@ -582,8 +574,9 @@ __global__ void __launch_bounds__(1024) mi_finalize(const unsigned long long* __
         const double p = (double)hist[q] * sc;
         float tv = 0.0f;
         if (p > 0.0) {
-            part += p * log(p / (pF[m] * pM[n]));
-            tv = (float)(log(p) - logM[n]);
+            const double t = log(p) - logM[n];  // one double logarithm per entry sets the time at many bins
+            part += p * (t - logF[m]);
+            tv = (float)t;
         }
         state[q] = tv;
         state[BB + q] = (float)p;
@@ -607,8 +600,9 @@ __global__ void __launch_bounds__(1024) mi_finalize(const unsigned long long* __
 // TP > 0: the log table is staged in LDS, padded (B <= MI_LDS_TABLE_BINS);
 // TP = 0: larger tables are read from the state through the caches.
 // (Compile-time, so the table reads are LDS or global loads, never flat.)
-template <bool HARD, int PAD, bool AFF, int TP>
-__global__ void __launch_bounds__(MI_NT) mi_grad_kernel(MiArgs a, const float* __restrict__ state,
+// TYB: rows of 64 threads in a block.
+template <bool HARD, int PAD, bool AFF, int TP, int TYB>
+__global__ void __launch_bounds__(MI_TX * TYB) mi_grad_kernel(MiArgs a, const float* __restrict__ state,
                                                         const float* __restrict__ grad_scale, float neg_inv_nroi,
                                                         float* __restrict__ gu)
 {
@@ -619,7 +613,7 @@ __global__ void __launch_bounds__(MI_NT) mi_grad_kernel(MiArgs a, const float* _
     // read from global memory with folded indices.
     extern __shared__ float Ts[];  // [TP * TP] when TP > 0
     const int B = a.bins;
-    for (int q = threadIdx.x; TP > 0 && q < TP * TP; q += MI_NT) {
+    for (int q = threadIdx.x; TP > 0 && q < TP * TP; q += MI_TX * TYB) {
         const int m = q / TP - 2, n = q % TP - 2;
         Ts[q] = (m < B + 2 && n < B + 2) ? state[fold(m, B) * B + fold(n, B)] : 0.0f;
     }
@@ -629,7 +623,7 @@ __global__ void __launch_bounds__(MI_NT) mi_grad_kernel(MiArgs a, const float* _
     const int bid = xcd_remap(blockIdx.x, a.nblocks);
     const int tx = bid % a.ntx, rest = bid / a.ntx, ty = rest % a.nty, ch = rest / a.nty;
     const int x = tx * MI_TX + (threadIdx.x % MI_TX);
-    const int y = ty * MI_TY + (threadIdx.x / MI_TX);
+    const int y = ty * TYB + (threadIdx.x / MI_TX);
     const int zb = ch * a.zchunk, ze = min(a.D, zb + a.zchunk);
     const int H = a.H, W = a.W, HW = H * W;
     const size_t N = (size_t)a.D * HW;
@@ -697,10 +691,10 @@ __global__ void __launch_bounds__(MI_NT) mi_grad_kernel(MiArgs a, const float* _
     }
     for (int z = s1; z < ze; ++z) store(z, 0.f, 0.f, 0.f);
     if (AFF) {
-        __shared__ double red[MI_NT];
+        __shared__ double red[MI_TX * TYB];
 #pragma unroll
         for (int q = 0; q < 12; ++q) {
-            const double v = block_sum<MI_NT>(acc[AFF ? q : 0], red);
+            const double v = block_sum<MI_TX * TYB>(acc[AFF ? q : 0], red);
             if (threadIdx.x == 0) a.apart[12 * (size_t)blockIdx.x + q] = v;
         }
     }
@@ -726,6 +720,58 @@ MiLaunch mi_plan(int rz, int ry, int rx)
     return L;
 }
 
+template <bool HARD, bool AFF, int TYB, bool GRP>
+static void mi_hist_pad(const MiArgs& a, int pad, size_t lds, unsigned long long* hist, unsigned long long* flag,
+                        hipStream_t st)
+{
+    const dim3 grid(a.nblocks), block(MI_TX * TYB);
+    if (pad == PAD_BORDER) hipLaunchKernelGGL((mi_hist_kernel<HARD, PAD_BORDER, AFF, TYB, GRP>), grid, block, lds, st, a, hist, flag);
+    else if (pad == MI_PAD_BORDER1) hipLaunchKernelGGL((mi_hist_kernel<HARD, MI_PAD_BORDER1, AFF, TYB, GRP>), grid, block, lds, st, a, hist, flag);
+    else hipLaunchKernelGGL((mi_hist_kernel<HARD, PAD_ZEROS, AFF, TYB, GRP>), grid, block, lds, st, a, hist, flag);
+}
+
+// Up to 56 bins, blocks of 256 threads with several histogram copies each (four
+// blocks on a CU at 32 bins).  Above, blocks of 1024 threads on one or two
+// copies, so that the larger histogram still leaves 16 waves or more to a CU: at
+// 64 bins 107 -> 95 us and at 98 132 -> 117 us (160 x 192 x 224; at 48 bins 90
+// against 91).  Histograms beyond MI_LDS_HIST (141 bins and more) are cut into
+// groups of F bins.  Adding taps straight into the global histogram instead,
+// as above 98 bins before, took 72 ms at 100 bins, now 0.11 ms: all blocks
+// meet on the few bins that the intensities fill.
+template <bool HARD, bool AFF>
+static void mi_hist_launch(const MiArgs& a0, int pad, unsigned long long* hist, unsigned long long* flag,
+                           hipStream_t st)
+{
+    MiArgs a = a0;
+    const int RP = mi_hist_pitch(a.bins);
+    a.ngroups = 1;
+    a.rows = a.bins;
+    if (a.bins <= 56) {
+        mi_hist_pad<HARD, AFF, MI_TY, false>(a, pad, sizeof(unsigned long long) * a.ncopy * (a.rows * RP + 1), hist, flag, st);
+        return;
+    }
+    constexpr int TYB = 16;
+    const int most = (MI_LDS_HIST - 8) / (RP * (int)sizeof(unsigned long long));  // rows of a group
+    a.ngroups = (a.bins + most - 1) / most;
+    a.rows = (a.bins + a.ngroups - 1) / a.ngroups;
+    if (a.ncopy == 0) a.ncopy = 1;
+    const int rz = a.roi[1] - a.roi[0], ry = a.roi[3] - a.roi[2];
+    a.nty = (ry + TYB - 1) / TYB;
+    const long long tiles = (long long)a.ntx * a.nty * a.ngroups;
+    const size_t lds = sizeof(unsigned long long) * ((size_t)a.ncopy * (a.rows * RP + 1));
+    // the fewest rounds of resident blocks times the slices of a block, its
+    // clearing and merging counted as 8
+    const int slots = 256 * (lds > 81920 ? 1 : 2);
+    long long best = -1;
+    for (int c = 1; c <= rz && (c == 1 || tiles * c <= 8192); ++c) {
+        const int zc = (rz + c - 1) / c, n = (rz + zc - 1) / zc;
+        const long long cost = ((tiles * n + slots - 1) / slots) * (zc + 8);
+        if (best < 0 || cost < best) { best = cost; a.zchunk = zc; a.nblocks = (int)(tiles * n); }
+    }
+    if (a.ngroups == 1) mi_hist_pad<HARD, AFF, TYB, false>(a, pad, lds, hist, flag, st);
+    else mi_hist_pad<HARD, AFF, TYB, true>(a, pad, lds, hist, flag, st);
+}
+
 template <bool AFF>
 static hipError_t mi_fwd_dispatch(const MiArgs& a, int hard, int pad, unsigned long long* hist,
                                   unsigned long long* flag, float* state, float* loss, hipStream_t st)
@@ -742,26 +788,8 @@ static hipError_t mi_fwd_dispatch(const MiArgs& a, int hard, int pad, unsigned l
         hipLaunchKernelGGL(mi_finalize_approx, dim3(1), dim3(1024), 0, st, hist, flag, a.bins, state, loss);
         return hipGetLastError();
     }
-    const size_t lds = sizeof(unsigned long long) * a.ncopy * (a.bins * mi_hist_pitch(a.bins) + 1);
-    if (a.ncopy == 0) {
-        if (hard) {
-            if (pad == PAD_BORDER) hipLaunchKernelGGL((mi_hist_kernel<true, PAD_BORDER, AFF, true>), grid, block, 0, st, a, hist, flag);
-            else if (pad == MI_PAD_BORDER1) hipLaunchKernelGGL((mi_hist_kernel<true, MI_PAD_BORDER1, AFF, true>), grid, block, 0, st, a, hist, flag);
-            else hipLaunchKernelGGL((mi_hist_kernel<true, PAD_ZEROS, AFF, true>), grid, block, 0, st, a, hist, flag);
-        } else {
-            if (pad == PAD_BORDER) hipLaunchKernelGGL((mi_hist_kernel<false, PAD_BORDER, AFF, true>), grid, block, 0, st, a, hist, flag);
-            else if (pad == MI_PAD_BORDER1) hipLaunchKernelGGL((mi_hist_kernel<false, MI_PAD_BORDER1, AFF, true>), grid, block, 0, st, a, hist, flag);
-            else hipLaunchKernelGGL((mi_hist_kernel<false, PAD_ZEROS, AFF, true>), grid, block, 0, st, a, hist, flag);
-        }
-    } else if (hard) {
-        if (pad == PAD_BORDER) hipLaunchKernelGGL((mi_hist_kernel<true, PAD_BORDER, AFF, false>), grid, block, lds, st, a, hist, flag);
-        else if (pad == MI_PAD_BORDER1) hipLaunchKernelGGL((mi_hist_kernel<true, MI_PAD_BORDER1, AFF, false>), grid, block, lds, st, a, hist, flag);
-        else hipLaunchKernelGGL((mi_hist_kernel<true, PAD_ZEROS, AFF, false>), grid, block, lds, st, a, hist, flag);
-    } else {
-        if (pad == PAD_BORDER) hipLaunchKernelGGL((mi_hist_kernel<false, PAD_BORDER, AFF, false>), grid, block, lds, st, a, hist, flag);
-        else if (pad == MI_PAD_BORDER1) hipLaunchKernelGGL((mi_hist_kernel<false, MI_PAD_BORDER1, AFF, false>), grid, block, lds, st, a, hist, flag);
-        else hipLaunchKernelGGL((mi_hist_kernel<false, PAD_ZEROS, AFF, false>), grid, block, lds, st, a, hist, flag);
-    }
+    if (hard) mi_hist_launch<true, AFF>(a, pad, hist, flag, st);
+    else mi_hist_launch<false, AFF>(a, pad, hist, flag, st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(mi_finalize, dim3(1), dim3(1024), 0, st, hist, flag, a.bins, state, loss);
@@ -775,10 +803,11 @@ hipError_t mi_fwd_launch(const MiArgs& a0, int hard, int pad, unsigned long long
     MiArgs a = a0;
     // LDS histogram copies: at most 4 and at most 79 KB (two blocks per CU).
     // u64 for the Parzen histogram, rows of mi_hist_pitch(B) entries: 4
-    // copies up to 47 bins, 2 up to 68, 1 up to 98; u32 counts of the
-    // approximate estimator within 66 KB: 1 copy up to 128 bins.  Larger
-    // histograms are added straight into the global one (ncopy = 0).
-    const size_t budget = hard == 2 ? 67584 : 80896;
+    // copies up to 47 bins, 2 up to 68, 1 up to 98, then see mi_hist_launch;
+    // u32 counts of the approximate estimator: within 66 KB up to 128 bins, one
+    // copy up to 199; larger counts are added straight into the global
+    // histogram (ncopy = 0).
+    const size_t budget = hard != 2 ? 80896 : a.bins <= 128 ? 67584 : MI_LDS_HIST;
     const size_t one = hard == 2 ? (size_t)(a.bins * a.bins + 1) * sizeof(unsigned int)
                                  : (size_t)(a.bins * mi_hist_pitch(a.bins) + 1) * sizeof(unsigned long long);
     a.ncopy = one <= budget ? 1 : 0;
@@ -793,16 +822,16 @@ hipError_t mi_fwd_launch(const MiArgs& a0, int hard, int pad, unsigned long long
                     : mi_fwd_dispatch<false>(a, hard, p, hist, flag, state, loss, st);
 }
 
-template <bool HARD, bool AFF, int TP>
+template <bool HARD, bool AFF, int TP, int TYB = MI_TY>
 static void mi_grad_launch_pad(int pad, dim3 grid, size_t lds, hipStream_t st, const MiArgs& a, const float* state,
                                const float* grad_scale, float nin, float* gu)
 {
     if (pad == PAD_BORDER)
-        hipLaunchKernelGGL((mi_grad_kernel<HARD, PAD_BORDER, AFF, TP>), grid, dim3(MI_NT), lds, st, a, state, grad_scale, nin, gu);
+        hipLaunchKernelGGL((mi_grad_kernel<HARD, PAD_BORDER, AFF, TP, TYB>), grid, dim3(MI_TX * TYB), lds, st, a, state, grad_scale, nin, gu);
     else if (pad == MI_PAD_BORDER1)
-        hipLaunchKernelGGL((mi_grad_kernel<HARD, MI_PAD_BORDER1, AFF, TP>), grid, dim3(MI_NT), lds, st, a, state, grad_scale, nin, gu);
+        hipLaunchKernelGGL((mi_grad_kernel<HARD, MI_PAD_BORDER1, AFF, TP, TYB>), grid, dim3(MI_TX * TYB), lds, st, a, state, grad_scale, nin, gu);
     else
-        hipLaunchKernelGGL((mi_grad_kernel<HARD, PAD_ZEROS, AFF, TP>), grid, dim3(MI_NT), lds, st, a, state, grad_scale, nin, gu);
+        hipLaunchKernelGGL((mi_grad_kernel<HARD, PAD_ZEROS, AFF, TP, TYB>), grid, dim3(MI_TX * TYB), lds, st, a, state, grad_scale, nin, gu);
 }
 
 // The padded LDS table pitch: the smallest of 36, 68, 132 that holds B + 4
@@ -819,8 +848,20 @@ static hipError_t mi_bwd_dispatch(const MiArgs& a, int hard, int pad, const floa
         mi_grad_launch_pad<false, AFF, 36>(pad, grid, sizeof(float) * 36 * 36, st, a, state, grad_scale, nin, gu);
     else if (B + 4 <= 68)
         mi_grad_launch_pad<false, AFF, 68>(pad, grid, sizeof(float) * 68 * 68, st, a, state, grad_scale, nin, gu);
-    else if (B <= MI_LDS_TABLE_BINS)
-        mi_grad_launch_pad<false, AFF, 132>(pad, grid, sizeof(float) * 132 * 132, st, a, state, grad_scale, nin, gu);
+    else if (B <= MI_LDS_TABLE_BINS) {
+        const size_t lds = sizeof(float) * 132 * 132;
+        if constexpr (AFF) {  // the caller counts the blocks' partials: blocks as planned
+            mi_grad_launch_pad<false, AFF, 132>(pad, grid, lds, st, a, state, grad_scale, nin, gu);
+        } else {
+            // 70 KB of table: 1024 threads share one (100 bins, 160 x 192 x 224: 103 -> 65 us)
+            MiArgs b = a;
+            b.nty = (a.H + 15) / 16;
+            const int tiles = b.ntx * b.nty, chunks = max(1, min((a.D + 3) / 4, 1024 / tiles));
+            b.zchunk = (a.D + chunks - 1) / chunks;
+            b.nblocks = tiles * ((a.D + b.zchunk - 1) / b.zchunk);
+            mi_grad_launch_pad<false, AFF, 132, 16>(pad, dim3(b.nblocks), lds, st, b, state, grad_scale, nin, gu);
+        }
+    }
     else
         mi_grad_launch_pad<false, AFF, 0>(pad, grid, 0, st, a, state, grad_scale, nin, gu);
     return hipGetLastError();

@@ -50,3 +50,23 @@ def test_smoothing_short_chunks(shape, sigma):
     out = ops.gaussian_smooth(x.to(DEV), sigma).cpu().numpy().astype(np.float64)
     ref = oracle.gaussian_smooth(x.numpy(), sigma)
     assert np.abs(out - ref).max() <= 1e-6 * max(1.0, np.abs(ref).max())
+
+
+# LDS histograms: the widest of 256-thread blocks and the first of 1024, one
+# copy at the edge of two blocks per CU, the largest whole histogram and the
+# first cut into two groups of F bins, three and four groups, both estimators
+@pytest.mark.parametrize("bins", [56, 57, 68, 69, 98, 99, 128, 129, 140, 141, 142, 199, 200, 213, 256])
+@pytest.mark.parametrize("shape,roi", [((9, 21, 70), None), ((18, 40, 34), ((2, 17), (3, 35), (1, 33)))])
+def test_mi_histogram_sizes(bins, shape, roi):
+    print(f"[mi histogram {shape} bins={bins} roi={roi}]", flush=True)
+    F, M, u = _pair(shape, 8)
+    r6 = None if roi is None else [v for k in roi for v in k]
+    l, st = ops.warp_mi_fwd(F.to(DEV), M.to(DEV), u.to(DEV), bins=bins, roi=roi)
+    g = ops.warp_mi_bwd(F.to(DEV), M.to(DEV), u.to(DEV), st, bins=bins, roi=roi)
+    lr, _, gr = oracle.mi(F.numpy(), M.numpy(), u.numpy(), bins=bins, roi=r6)
+    assert_loss(float(l.item()), lr, "loss")
+    assert_grad(g.cpu().numpy(), gr, "grad")
+    l2, st2 = ops.warp_mi_fwd(F.to(DEV), M.to(DEV), u.to(DEV), bins=bins, roi=roi)
+    assert torch.equal(st, st2) and torch.equal(l, l2)  # integer sums: the same bits every time
+    pmf = st[bins * bins:2 * bins * bins].double().cpu()
+    assert abs(float(pmf.sum()) - 1.0) < 1e-5

@@ -391,7 +391,13 @@ hipError_t wide_run(int mode, const WideArgs& a, const WidePlan& P, hipStream_t 
 }  // namespace
 
 // z passes: 64 x 4 columns per block, z-chunks of at least 32 slices, about
-// 4096 blocks where the volume allows.
+// 4096 blocks where the volume allows; where that leaves fewer than 1024 blocks
+// (the z kernels are a serial chain per column and need 4 blocks per CU to cover
+// it), the chunk length with the fewest rounds of 1024 times the slices of a
+// block, the sum of its first window counted as 8.  w = 11, chunks of 32 ->
+// this rule: 48 x 60 x 80 (30 -> 720 blocks) z 42 -> 14 us, grad 76 -> 11 us;
+// 100 x 120 x 140 (270 -> 900 blocks) z 41 -> 43 us, grad 63 -> 30 us;
+// 160 x 192 x 224 has 960 blocks either way.
 WidePlan wide_plan(int D, int H, int W)
 {
     WidePlan P;
@@ -402,6 +408,14 @@ WidePlan wide_plan(int D, int H, int W)
     const long long most = max(1, D / 32);
     if (want > most) want = most;
     if (want < 1) want = 1;
+    if (cols * want < 1024) {
+        long long best = -1;
+        for (int n = 1; n <= D && n <= 1024; ++n) {
+            const int zc = (D + n - 1) / n;
+            const long long cost = (cols * n + 1023) / 1024 * (zc + 8);
+            if (best < 0 || cost < best) { best = cost; want = n; }
+        }
+    }
     P.zchunk = (int)((D + want - 1) / want);
     P.nchunks = (D + P.zchunk - 1) / P.zchunk;
     P.nblocks = (int)(cols * P.nchunks);

@@ -19,7 +19,8 @@ def _pair(shape, seed):
 
 
 @pytest.mark.parametrize("shape,window", [((2, 25, 33), 3), ((13, 24, 32), 9), ((37, 17, 65), 5),
-                                          ((40, 48, 56), 7)])
+                                          ((40, 48, 56), 7), ((3, 25, 33), 15), ((61, 70, 90), 11),
+                                          ((33, 130, 257), 13)])
 def test_lncc_short_chunks(shape, window):
     print(f"[lncc short chunks {shape} w={window}]", flush=True)
     F, M, u = _pair(shape, 5)

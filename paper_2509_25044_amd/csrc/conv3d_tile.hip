@@ -32,11 +32,11 @@
 // Bound and rates, clinical batch of 4 (ms, against a kernel that gathered
 // both operands per lane from global memory): matrix issue for 48 -> 16 at full
 // resolution, 4.85 -> 1.04 (1090 TFLOP/s; MFMA busy 0.56 of the SIMD cycles),
-// 96 -> 32 1.73 -> 0.65, 192 -> 64 0.82 -> 0.40; staging and stores for the
+// 96 -> 32 1.73 -> 0.57, 192 -> 64 0.82 -> 0.37; staging and stores for the
 // thin layers, 4 -> 16 1.38 -> 0.48, 16 -> 4 2.02 -> 0.49, 16 -> 32 stride 2
 // 0.53 -> 0.32 (2.2 to 2.9 TB/s).  Input gradients: 16 -> 48 3.66 -> 1.68 (3.7
-// TB/s, the fp32 gradient's write), 32 -> 96 1.56 -> 0.73, 64 -> 192 1.25 ->
-// 0.41, 4 -> 16 1.09 -> 0.54.  One clinical volume, 192 -> 64: 0.22 -> 0.13.
+// TB/s, the fp32 gradient's write), 32 -> 96 1.56 -> 0.66, 64 -> 192 1.25 ->
+// 0.35, 4 -> 16 1.09 -> 0.54.  One clinical volume, 192 -> 64: 0.22 -> 0.11.
 #include "conv_p.hpp"
 #include "conv_tile.hpp"
 #include "device.hpp"
@@ -452,7 +452,7 @@ struct WdTile {
     static constexpr int XB = (XU > UXU ? XU : UXU);             // ... of a buffer
     static constexpr int WB = WN * 9 * 64;
     static constexpr int LDS = 2 * (XB + WB) * 16;
-    static constexpr int NU = (XU + NT - 1) / NT, XR = S * (RW - 1) + 3;
+    static constexpr int NU = (XU + NT - 1) / NT, NUX = (UXU + NT - 1) / NT, XR = S * (RW - 1) + 3;
     static constexpr int div(int w) { return (65536 + w - 1) / w; }
     static constexpr bool div_ok(int w, int n)
     {
@@ -519,12 +519,59 @@ __global__ void __launch_bounds__(64 * WR * WN, 2) conv_wide_kernel(TcArgs a)
             }
         }
     };
+    // What the loads' addresses need of a lane is the same in every step: the
+    // channels of its chunk, the voxel of each of its units in a slice (-1
+    // outside), its weight row.  Worked out per load this was about 45
+    // instructions for each of a sub-step's 5 to 8 loads, beside 72 products
+    // (batch of 4: 192 -> 64 0.43 -> 0.37 ms, 96 -> 32 0.68 -> 0.57 ms).
+    constexpr bool FAST = C8 && !FROMDY;
+    const int ch8 = 8 * ((tid & 3) ^ ((tid >> 3) & 3));
+    int vox[FAST ? T::NU : 1], uvox[FAST && TWO ? T::NUX : 1];
+    const int wrow = n0 + wn * 16 + ((tid & 63) >> 2);
+    const bool wok = wrow < a.Nout;
+    const gptr wl = as_global(a.w) + (size_t)(wok ? wrow : 0) * 27 * Cin + ch8;
+    if constexpr (FAST) {
+        auto voxel = [&](int u, int us, int w, int rw, int n) __attribute__((always_inline)) {
+            const int p = (u * (T::NT / 64) + wave) * 64 + (tid & 63);
+            const int v = p >> 2, vy = (int)(__umul24(v, rw) >> 16), sW = a.Wi >> us, sH = a.Hi >> us;
+            const int X = (x0 >> us) - 1 + v - (int)__umul24(vy, w), Y = (y0 >> us) - 1 + vy;
+            return p < n && (unsigned)X < (unsigned)sW && (unsigned)Y < (unsigned)sH ? Y * sW + X : -1;
+        };
+        static_assert(!FAST || S == 1, "columns of a stride-2 slice are reordered");
+#pragma unroll
+        for (int u = 0; u < T::NU; ++u) vox[u] = voxel(u, 0, T::XP, T::div(T::XP), T::XU);
+        if constexpr (TWO) {
+#pragma unroll
+            for (int u = 0; u < T::NUX; ++u) uvox[u] = voxel(u, 1, T::UXP, T::div(T::UXP), T::UXU);
+        }
+    }
+    const gptr zero = as_global(&tc_zero);
+    auto fetch = [&](uint4* dst, bool ok, gptr p) __attribute__((always_inline)) {
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(ok ? p : zero), (ldsptr)dst, 16,
+                                         0, 0);
+    };
     // slice k of group g (of part a while g < na) into buffer xd
     auto load_x = [&](uint4* xd, int k, int g) __attribute__((always_inline)) {
         const bool pa = g < a.na, ups = TWO && pa;
         const int us = ups ? 1 : 0;
         const int C = pa ? a.Ca : a.Cb, c0 = 32 * (pa ? g : g - a.na);
         const gptr src = as_global(pa ? a.xa : a.xb);
+        if constexpr (FAST) {
+            const int zi = (z0 - 1 + k) >> us, sD = a.Di >> us;
+            const bool zok = (unsigned)zi < (unsigned)sD && ch8 < C - c0;
+            const gptr sb = src + ((size_t)bn * sD + max(0, min(zi, sD - 1))) * ((size_t)(a.Hi >> us) * (a.Wi >> us)) * C + c0;
+            auto units = [&](const int* vo, int nu, int n) __attribute__((always_inline)) {
+#pragma unroll
+                for (int u = 0; u < nu; ++u) {
+                    const int p0 = (u * (T::NT / 64) + wave) * 64;
+                    if (p0 < n && (tid & 63) < n - p0)  // a buffer's last units: lanes past it stay out
+                        fetch(xd + p0, zok && vo[u] >= 0, sb + ((size_t)(unsigned)vo[u] * (unsigned)C + ch8));
+                }
+            };
+            if (TWO && ups) units(uvox, T::NUX, T::UXU);
+            else units(vox, T::NU, T::XU);
+            return;
+        }
         const int sW = a.Wi >> us, sH = a.Hi >> us, sD = a.Di >> us;
         const int bx = (S * x0 >> us) - 1, by = (S * y0 >> us) - 1, zi = (S * z0 - 1 + k) >> us;
         const bool zok = (unsigned)zi < (unsigned)sD;
@@ -567,11 +614,17 @@ __global__ void __launch_bounds__(64 * WR * WN, 2) conv_wide_kernel(TcArgs a)
     auto load_w = [&](uint4* wd, int k, int g, int dx) __attribute__((always_inline)) {
         const bool pa = g < a.na;
         const int C = pa ? a.Ca : a.Cb, c0 = 32 * (pa ? g : g - a.na);
+        const bool ok = wok && ch8 < C - c0;
+        const gptr wg = wl + ((pa ? 0 : a.Ca) + c0);
 #pragma unroll
         for (int u = 0; u < (9 + WR - 1) / WR; ++u) {
             const int f = u * WR + wr;
             if (f >= 9 || !tc_used<S>(k, f / 3, nz)) continue;  // what no output slice needs is not fetched
             const int tap = GRAD ? 26 - (f * 3 + dx) : f * 3 + dx;
+            if constexpr (FAST) {
+                fetch(wd + (wn * 9 + f) * 64, ok, wg + (size_t)(unsigned)(tap * Cin));
+                continue;
+            }
             dma(wd + (wn * 9 + f) * 64, 64, [&](int l, gptr& p, int& nc) __attribute__((always_inline)) {
                 const int li = l >> 2, n = n0 + wn * 16 + li, c = c0 + 8 * ((l & 3) ^ ((li >> 1) & 3));
                 nc = n < a.Nout ? C - c : 0;

@@ -36,7 +36,7 @@
 // thin layers, 4 -> 16 1.38 -> 0.48, 16 -> 4 2.02 -> 0.49, 16 -> 32 stride 2
 // 0.53 -> 0.32 (2.2 to 2.9 TB/s).  Input gradients: 16 -> 48 3.66 -> 1.68 (3.7
 // TB/s, the fp32 gradient's write), 32 -> 96 1.56 -> 0.66, 64 -> 192 1.25 ->
-// 0.35, 4 -> 16 1.09 -> 0.54.  One clinical volume, 192 -> 64: 0.22 -> 0.11.
+// 0.35, 4 -> 16 1.09 -> 0.54.  One clinical volume, 192 -> 64: 0.22 -> 0.10.
 #include "conv_p.hpp"
 #include "conv_tile.hpp"
 #include "device.hpp"
@@ -467,7 +467,7 @@ struct WdTile {
 
 typedef __attribute__((address_space(3))) void* ldsptr;
 
-template <int S, int RW, int WR, int WN, bool TWO, bool C8, bool FROMDY, bool GRAD>
+template <int S, int RW, int WR, int WN, bool TWO, bool C8, bool FROMDY, bool GRAD, bool ZO>
 __global__ void __launch_bounds__(64 * WR * WN, 2) conv_wide_kernel(TcArgs a)
 {
     using T = WdTile<S, RW, WR, WN>;
@@ -610,8 +610,8 @@ __global__ void __launch_bounds__(64 * WR * WN, 2) conv_wide_kernel(TcArgs a)
             }
         }
     };
-    // the wave's share of the 9 (dz, dy) fragments of its tile at x shift dx
-    auto load_w = [&](uint4* wd, int k, int g, int dx) __attribute__((always_inline)) {
+    // the wave's share of the 9 fragments of its tile at x shift d, (dz, dy), or (ZO) at z tap d, (dy, dx)
+    auto load_w = [&](uint4* wd, int k, int g, int d) __attribute__((always_inline)) {
         const bool pa = g < a.na;
         const int C = pa ? a.Ca : a.Cb, c0 = 32 * (pa ? g : g - a.na);
         const bool ok = wok && ch8 < C - c0;
@@ -619,8 +619,8 @@ __global__ void __launch_bounds__(64 * WR * WN, 2) conv_wide_kernel(TcArgs a)
 #pragma unroll
         for (int u = 0; u < (9 + WR - 1) / WR; ++u) {
             const int f = u * WR + wr;
-            if (f >= 9 || !tc_used<S>(k, f / 3, nz)) continue;  // what no output slice needs is not fetched
-            const int tap = GRAD ? 26 - (f * 3 + dx) : f * 3 + dx;
+            if (f >= 9 || (!ZO && !tc_used<S>(k, f / 3, nz))) continue;  // what no output slice needs is not fetched
+            const int t = ZO ? 9 * d + f : 3 * f + d, tap = GRAD ? 26 - t : t;
             if constexpr (FAST) {
                 fetch(wd + (wn * 9 + f) * 64, ok, wg + (size_t)(unsigned)(tap * Cin));
                 continue;
@@ -640,9 +640,68 @@ __global__ void __launch_bounds__(64 * WR * WN, 2) conv_wide_kernel(TcArgs a)
     };
 
     load_x(xs, 0, 0);
-    load_w(ws, 0, 0, shift(0));
+    load_w(ws, 0, 0, ZO ? 0 : shift(0));
     arrive();
     int par = 0, wpar = 0;
+    if constexpr (ZO) {
+        for (int k = 0; k < nk; ++k) {
+            for (int g = 0; g < a.ng; ++g) {
+                const bool last = g + 1 == a.ng, more = !last || k + 1 < nk;
+                const int kn = last ? k + 1 : k, gn = last ? 0 : g + 1;
+                const bool ups = TWO && g < a.na;
+                const int d0 = max(0, k - nz + 1), d1 = min(2, k);  // z taps that an output slice needs
+                for (int dz = d0; dz <= d1; ++dz) {
+                    const uint4* const xb = xs + par * T::XB;
+                    const uint4* const wb = ws + wpar * T::WB;
+                    for (int di = 0; di < 3; ++di) {
+                        const int dx = shift(di);
+                        uint4 X[T::XR], w[3];
+                        if (active) {
+                            const int lane = opaque(tid & 63), li = lane & 15, kg = lane >> 4;
+                            const int px = ups ? (li + dx + 1) >> 1 : li + dx, r0 = RW * wr;
+                            const int v0 = px + (ups ? (r0 / 2) * T::UXP : r0 * T::XP);
+                            int at[4];  // rows r, r + 4, ... share the XOR pattern
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) at[e] = 4 * v0 + (kg ^ (((v0 >> 1) + e) & 3));
+#pragma unroll
+                            for (int r = 0; r < T::XR; ++r) {
+                                const int ur = (r + 1) >> 1;
+                                X[r] = ups ? xb[at[ur & 3] + ur * T::UXP * 4] : xb[at[r & 3] + r * T::XP * 4];
+                            }
+                            const uint4* const ww = wb + wn * 9 * 64 + li * 4 + (kg ^ ((li >> 1) & 3));
+#pragma unroll
+                            for (int dy = 0; dy < 3; ++dy) w[dy] = ww[(3 * dy + dx) * 64];
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (di == 0) {
+                            if (dz < d1) load_w(ws + (wpar ^ 1) * T::WB, k, g, dz + 1);
+                            else if (more) load_w(ws + (wpar ^ 1) * T::WB, kn, gn, max(0, kn - nz + 1));
+                            if (dz == d0 && more) load_x(xs + (par ^ 1) * T::XB, kn, gn);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (active) {
+#pragma unroll
+                            for (int s = 0; s < 3; ++s)
+                                if (s == dz) {
+#pragma unroll
+                                    for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+                                        for (int yo = 0; yo < RW; ++yo)
+                                            acc[tc_slot<S>(s)][yo] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                                as_bf8(w[dy]), as_bf8(X[yo + dy]), acc[tc_slot<S>(s)][yo], 0, 0, 0);
+                                }
+                        }
+                    }
+                    if (active && dz == d1 && last)
+                        tc_advance<S, RW, GRAD>(a, acc, k, bn, z0, y0 + wr * RW, x0, n0 + wn * 16);
+                    wpar ^= 1;
+                    arrive();
+                }
+                par ^= 1;
+            }
+        }
+        return;
+    }
     for (int k = 0; k < nk; ++k) {
         for (int g = 0; g < a.ng; ++g) {
             const bool last = g + 1 == a.ng, more = !last || k + 1 < nk;
@@ -723,8 +782,20 @@ hipError_t wd_launch(TcArgs& a, hipStream_t st)
     a.ng = a.na + (a.Cb + 31) / 32;
     const hipError_t e = tc_plan(a, a.Do, a.Ho, a.Wo, T::YT, WN, tc_resident_blocks(T::LDS, T::NT, RW));
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((conv_wide_kernel<S, RW, WR, WN, TWO, C8, FROMDY, GRAD>), dim3((unsigned)a.nblocks), dim3(T::NT),
-                       T::LDS, st, a);
+    // Output chunks of one or two slices need 3 of 9 or 6 of 12 z taps of the input slices they stage: sub-steps by z
+    // tap (9 products' fragments of each x shift of one tap) then do without the rest, where sub-steps by x shift are
+    // as many as ever and a third or half full (192 -> 64: one 64 x 64 x 64 volume, 1 slice, 70 -> 55 us; 160 x 192 x
+    // 224, 2 slices, 107 -> 103 us).  From 3 slices on, reading the rows once per x shift outweighs it.  A single
+    // channel tile's rows leave no registers for it.
+    if constexpr (S == 1 && C8 && !FROMDY && WN > 1) {
+        if (a.zlen <= 2) {
+            hipLaunchKernelGGL((conv_wide_kernel<S, RW, WR, WN, TWO, C8, FROMDY, GRAD, true>), dim3((unsigned)a.nblocks),
+                               dim3(T::NT), T::LDS, st, a);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((conv_wide_kernel<S, RW, WR, WN, TWO, C8, FROMDY, GRAD, false>), dim3((unsigned)a.nblocks),
+                       dim3(T::NT), T::LDS, st, a);
     return hipGetLastError();
 }
 

@@ -66,6 +66,8 @@ DATA_CASES = [
     (1, 2, 9, 5, 40, 24, 96, 1, False),
     (1, 2, 17, 16, 32, 32, 80, 1, False),
     (1, 3, 8, 16, 68, 0, 64, 1, False),
+    (2, 20, 40, 34, 16, 8, 64, 1, True),  # wide layers: z chunks of 2 slices, then of 3
+    (2, 40, 40, 34, 16, 8, 64, 1, True),
     (1, 9, 15, 33, 16, 0, 32, 2, False),
     (1, 4, 17, 31, 8, 0, 64, 2, False),
     (2, 3, 16, 35, 32, 0, 48, 2, False),

@@ -330,10 +330,14 @@ __device__ __forceinline__ void lncc_reference(const float* __restrict__ F, cons
 
 // Held to 128 VGPRs where 16 waves share a CU (1024-thread blocks, or two
 // 512-thread blocks for windows up to 5); a 768-thread block is held to 168
-// by its launch bound.  ADDR: see ld().
+// by its launch bound.  The forward at w = 3 would fit three blocks to a CU,
+// which leaves the last round of the plan's chunks, cut for two, to few of them:
+// held to two (320 x 320 x 320: 331 -> 298 us; planned for three 339 us, and 512
+// x 512 x 512 1279 against 1117 us).  ADDR: see ld().
 template <int WIN, int MODE, int PAD, int ADDR, int TX_, int TY_>
 __global__ void __launch_bounds__(TX_ * TY_)
-    __attribute__((amdgpu_waves_per_eu((TX_ * TY_ >= 1024 || WIN <= 5 || MODE == MODE_ACE || MODE == MODE_FWD) ? 4 : 2, 8)))
+    __attribute__((amdgpu_waves_per_eu((TX_ * TY_ >= 1024 || WIN <= 5 || MODE == MODE_ACE || MODE == MODE_FWD) ? 4 : 2,
+                                         WIN == 3 && MODE == MODE_FWD ? 5 : 8)))
 lncc_kernel(LnccArgs a)
 {
     using T = LnccTile<WIN, MODE, TX_, TY_>;

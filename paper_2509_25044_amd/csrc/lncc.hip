@@ -300,32 +300,29 @@ __device__ __forceinline__ Tri interp_pending(const Pend& g)
     return t;
 }
 
-// The value that the fields of the split adjoint are taken relative to: the
-// mean of 64 grid samples, the same in every block.  sum a (F - ref) - c (Mw -
-// ref) cancels less the nearer ref lies to the values (a mean does as well as
-// a value of the tile; a reference of 0 doubles the gradient's rounding
-// error).  Samples that are not finite are left out.
-__device__ __forceinline__ void lncc_reference(const float* __restrict__ F, const float* __restrict__ M, int D, int H,
-                                               int W, float& rf, float& rm)
+// The values that the a, c, e sums of a tile (32 x 16 columns of the z chunk z0
+// .. z1) are taken relative to in the split adjoint: the median of three rows'
+// medians of 3 x 3 samples of its middle slice.  A mean would lie between the
+// levels of a tile with an edge in it; one sample, as the shift of the
+// statistics, lies a deviation of the texture off, and the gradient's rounding
+// error on white noise was 15% above the one-kernel adjoint's.
+__device__ __forceinline__ void ace_reference(const float* __restrict__ F, const float* __restrict__ M, int D, int H,
+                                              int W, int z0, int z1, int tx, int ty, float& rf, float& rm)
 {
-    const int l = threadIdx.x & 63;
-    const int x = (int)((2ll * (l & 3) + 1) * W / 8), y = (int)((2ll * ((l >> 2) & 3) + 1) * H / 8);
-    const int z = (int)((2ll * (l >> 4) + 1) * D / 8);
-    const size_t i = ((size_t)z * H + y) * W + x;
-    rf = F[i];
-    rm = M[i];
+    const size_t z = (size_t)min((z0 + z1) / 2, D - 1) * H;
+    const int x0 = min(32 * tx + 5, W - 1), x1 = min(32 * tx + 16, W - 1), x2 = min(32 * tx + 26, W - 1);
+    float f[3], m[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const size_t row = (z + min(16 * ty + 2 + 6 * k, H - 1)) * W;
+        f[k] = __builtin_amdgcn_fmed3f(F[row + x0], F[row + x1], F[row + x2]);
+        m[k] = __builtin_amdgcn_fmed3f(M[row + x0], M[row + x1], M[row + x2]);
+    }
+    rf = __builtin_amdgcn_fmed3f(f[0], f[1], f[2]);
+    rm = __builtin_amdgcn_fmed3f(m[0], m[1], m[2]);
     const bool ok = fabsf(rf) < 1e30f && fabsf(rm) < 1e30f;
-    float n = ok ? 1.0f : 0.0f;
     rf = ok ? rf : 0.0f;
     rm = ok ? rm : 0.0f;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        rf += __shfl_xor(rf, o);
-        rm += __shfl_xor(rm, o);
-        n += __shfl_xor(n, o);
-    }
-    rf = n > 0.0f ? rf / n : 0.0f;
-    rm = n > 0.0f ? rm / n : 0.0f;
 }
 
 // Held to 128 VGPRs where 16 waves share a CU (1024-thread blocks, or two
@@ -428,7 +425,8 @@ lncc_kernel(LnccArgs a)
     float rA[MODE == MODE_ACE ? 3 : 1][WIN];       // a, c, e of the tile voxel: last w slices
     float refF = 0.f, refM = 0.f;
     if (MODE == MODE_ACE) {
-        lncc_reference(F, M, D, H, W, refF, refM);
+        static_assert(MODE != MODE_ACE || (TX == 32 && TY == 16), "the tiles of ace_reference");
+        ace_reference(F, M, D, H, W, z0, z1, gx0 / TX, gy0 / TY, refF, refM);
         refF = sF - refF;
         refM = sM - refM;
 #pragma unroll
@@ -759,13 +757,27 @@ lncc_kernel(LnccArgs a)
 // of one column: y-windows, the sampler's derivative from gathers issued at
 // the start of the step (u a step ahead), gradient.  The block after the last
 // slice reduces the loss partials (as lncc_finalize).
+//
+// sum a (F - s) - c (Mw - s') + e holds for any s, s' that all of a window's e
+// are relative to, and cancels the less the nearer they lie to the values
+// there: with one pair for the whole volume the gradient of a plateau of level L
+// and contrast q was off by about L / q rounding errors (levels 0 and 1000,
+// contrast 1: 7e-5 of its maximum against 2e-7).  So the sums of a tile stay
+// relative to its own pair (ace_reference; all of a slice's in LDS), and what a window
+// takes from the tile beside it is moved to the tile of its centre: e += c (s'
+// there - s' here) - a (s there - s here).  The x pass does that for columns, and
+// for rows once their x-windows are formed: the outputs of a step lie in one row of
+// tiles, so the chunk's rows of the row of tiles below are moved up for it, kept as
+// they were as well, and put back when that row's turn comes, where the last rows
+// of the tiles above are moved down.
 template <int WIN, int RB, int NT>
 __global__ void __launch_bounds__(NT) lncc_xy_kernel(LnccArgs a, int npart, double inv_nroi, float* loss)
 {
     constexpr int r = (WIN - 1) / 2, NV = WIN + 3;
     constexpr float inv = 1.0f / float(WIN * WIN * WIN);
     static_assert(2 * r <= RB && r <= 4 && RB % 4 == 0, "a window spans two chunks of rows, a run three float4");
-    extern __shared__ float xf[];  // [3 fields][2 chunks][RB][PW], then the chunk laid in [3][RB][PW + 8]
+    // [3 fields][2 chunks][RB][PW], the chunk laid in [3][RB][PW + 8], kept rows [r][PW], the tiles' references
+    extern __shared__ float xf[];
     const int tid = threadIdx.x;
     const int D = a.D, H = a.H, W = a.W, HW = H * W;
     const int z = xcd_remap(blockIdx.x, gridDim.x);
@@ -776,11 +788,10 @@ __global__ void __launch_bounds__(NT) lncc_xy_kernel(LnccArgs a, int npart, doub
         if (tid == 0) *loss = (float)(1.0 - s * inv_nroi);
         return;
     }
-    float refF, refM;
-    lncc_reference(a.F, a.M, D, H, W, refF, refM);
     const size_t N = (size_t)D * HW;
     const int NR = (W + 3) >> 2, PW = 4 * NR, FS = 2 * RB * PW, RS = RB * (PW + 8);
     float* const raw = xf + 3 * FS;
+    float2* const tref = reinterpret_cast<float2*>(raw + 3 * RS + r * PW);  // [nty][ntx]
     float* const G[3] = {a.gu, a.gu + N, a.gu + 2 * N};
     const unsigned zoff = (unsigned)z * (unsigned)HW;
 
@@ -814,19 +825,46 @@ __global__ void __launch_bounds__(NT) lncc_xy_kernel(LnccArgs a, int npart, doub
 #pragma unroll
         for (int f = 0; f < 3; ++f) *reinterpret_cast<float4*>(rawp + f * RS + 4) = make_float4(v[f].x, v[f].y, v[f].z, v[f].w);
     };
+    // e of 4 columns, relative to `from`, relative to `to`
+    auto move = [&](float4 e, const float* pa, const float* pc, float2 from, float2 to) {
+        const float4 ga = *reinterpret_cast<const float4*>(pa), gc = *reinterpret_cast<const float4*>(pc);
+        const float dF = from.x - to.x, dM = from.y - to.y;
+        return make_float4(e.x + fmaf(gc.x, dM, -ga.x * dF), e.y + fmaf(gc.y, dM, -ga.y * dF),
+                           e.z + fmaf(gc.z, dM, -ga.z * dF), e.w + fmaf(gc.w, dM, -ga.w * dF));
+    };
+    float* const keep = raw + 3 * RS + (xrow - (RB - r)) * PW + 4 * xrun;  // of rows RB - r .. RB - 1 of a chunk
+    // x-windows of chunk c, for the outputs of step c - 1, all in tile row T
     auto xpass = [&](int c) {
         if (!xact) return;
+        const int T = max(RB * (c - 1), 0) >> 4, y = RB * (c - 1) + r + xrow;
+        const float2* const sh = tref + (xrun >> 3);
         float* const dst = xf + ((c & 1) * RB + xrow) * PW + 4 * xrun;
+        if (c > 1 && ((RB * (c - 1)) & 15) == 0 && xrow >= RB - 2 * r) {  // rows of the chunk before, on either side of T's border
+            float* const old = xf + ((1 - (c & 1)) * RB + xrow) * PW + 4 * xrun;
+            float4* const pe = reinterpret_cast<float4*>(old + 2 * FS);
+            if (xrow >= RB - r) *pe = *reinterpret_cast<const float4*>(keep);
+            else *pe = move(*pe, old, old + FS, sh[(T - 1) * a.ntx], sh[T * a.ntx]);
+        }
+        const int ty = min(max(y, 0), H - 1) >> 4;
+        // 4 columns at a time: group 0 or 2 is the next tile's where a run is its tile's first or last
+        const bool left = (xrun & 7) == 0 && xrun > 0, right = (xrun & 7) == 7 && xrun + 1 < NR;
 #pragma unroll
         for (int f = 0; f < 3; ++f) {
             float t[12], o[4];
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
-                const float4 q = reinterpret_cast<const float4*>(rawp + f * RS)[k];
+                float4 q = reinterpret_cast<const float4*>(rawp + f * RS)[k];
+                if (f == 2 && k == 0 && left) q = move(q, rawp, rawp + RS, sh[ty * a.ntx - 1], sh[ty * a.ntx]);
+                if (f == 2 && k == 2 && right) q = move(q, rawp + 8, rawp + 8 + RS, sh[ty * a.ntx + 1], sh[ty * a.ntx]);
                 t[4 * k] = q.x; t[4 * k + 1] = q.y; t[4 * k + 2] = q.z; t[4 * k + 3] = q.w;
             }
             win4<WIN>(t + 4 - r, o);
-            *reinterpret_cast<float4*>(dst + f * FS) = make_float4(o[0], o[1], o[2], o[3]);
+            float4 w = make_float4(o[0], o[1], o[2], o[3]);
+            if (f == 2 && (y >> 4) > T) {  // T + 1's rows, at the end of a chunk
+                *reinterpret_cast<float4*>(keep) = w;
+                w = move(w, dst, dst + FS, sh[min(T + 1, a.nty - 1) * a.ntx], sh[T * a.ntx]);
+            }
+            *reinterpret_cast<float4*>(dst + f * FS) = w;
         }
     };
     for (int q = tid; q < 3 * RB * 8; q += NT)  // the 4 columns left and right of the rows stay zero
@@ -842,6 +880,15 @@ __global__ void __launch_bounds__(NT) lncc_xy_kernel(LnccArgs a, int npart, doub
     };
     load_rows(0);
     if (yact) load_u(0);
+    {
+        const int z0 = z / a.zchunk * a.zchunk, z1 = min(D, z0 + a.zchunk);
+        for (int q = tid; q < a.ntx * a.nty; q += NT) {
+            const int ty = q / a.ntx;
+            float2 s;
+            ace_reference(a.F, a.M, D, H, W, z0, z1, q - ty * a.ntx, ty, s.x, s.y);
+            tref[q] = s;
+        }
+    }
     lay();
     load_rows(1);
     __syncthreads();
@@ -882,11 +929,12 @@ __global__ void __launch_bounds__(NT) lncc_xy_kernel(LnccArgs a, int npart, doub
                 for (int n = 0; n < NV; ++n) v[n] = xf[f * FS + at[n]];
                 win4<WIN>(v, A[f]);
             }
+            const float2 s = tref[(y0 >> 4) * a.ntx + (x >> 5)];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int y = y0 + e;
                 const Tri t = interp_pending<true>(g[e]);
-                const float gm = fmaf(g[e].f - refF, A[0][e], fmaf(refM - t.v, A[1][e], A[2][e])) * inv;
+                const float gm = fmaf(g[e].f - s.x, A[0][e], fmaf(s.y - t.v, A[1][e], A[2][e])) * inv;
                 if (y < H) {
                     const unsigned id = zoff + __umul24((unsigned)y, (unsigned)W) + x;
                     st<LNCC_ADDR32>(G[0], id, gm * t.dx);
@@ -974,6 +1022,12 @@ LnccLaunch lncc_plan(int D, int H, int W, int win, int mode)
 // rows per thread, and 3 RB (3 W + 8) floats of LDS.  W <= LNCC_XY_MAX_W.
 constexpr int LNCC_XY_MAX_W = 512;
 static int xy_rows(int W) { return W <= 256 ? 16 : 8; }
+// LDS bytes of lncc_xy_kernel: rows and windows, kept rows, 8 bytes for each tile of a slice
+static long long xy_lds(int win, int RB, int W, const LnccLaunch& S)
+{
+    const int PW = (W + 3) & ~3;
+    return 12LL * RB * (3 * PW + 8) + 4LL * (win / 2) * PW + 8LL * S.ntx * S.nty;
+}
 
 // Does the adjoint of this shape run as two kernels (MODE_ACE, lncc_xy_kernel)?
 // Windows 7 and 9, whose fused kernel samples 2 and 3 points per output and
@@ -990,7 +1044,7 @@ static bool lncc_split(int D, int H, int W, int win, int pad)
 {
     if (win < 7 || pad != PAD_BORDER || W > LNCC_XY_MAX_W) return false;
     const LnccLaunch S = lncc_plan(D, H, W, win, MODE_ACE), B = lncc_plan(D, H, W, win, MODE_BWD);
-    if (S.addr != LNCC_ADDR32) return false;
+    if (S.addr != LNCC_ADDR32 || xy_lds(win, xy_rows(W), W, S) > 160 * 1024) return false;
     const int halo = 2 * (win - 1), RB = xy_rows(W);
     const double fused = (win == 7 ? 4.6 : 4.1) * ((B.nblocks + 255) / 256) * (B.zchunk + halo);
     const double first = (S.nblocks <= 256 ? 2.2 : win == 7 ? 3.7 : 4.3) * ((S.nblocks + 511) / 512) * (S.zchunk + halo);
@@ -1048,25 +1102,25 @@ static hipError_t launch_mode(int win, int pad, const LnccLaunch& L, const LnccA
 }
 
 template <int WIN, int RB, int NT>
-static hipError_t launch_xy(const LnccArgs& a, float* loss, double nroi, hipStream_t st)
+static hipError_t launch_xy(const LnccLaunch& S, const LnccArgs& a, float* loss, double nroi, hipStream_t st)
 {
-    const int PW = (a.W + 3) & ~3, lds = 3 * RB * (3 * PW + 8) * (int)sizeof(float);
+    const int lds = (int)xy_lds(WIN, RB, a.W, S);
     hipLaunchKernelGGL((lncc_xy_kernel<WIN, RB, NT>), dim3(a.D + (loss ? 1 : 0)), dim3(NT),
                        max(lds, NT * (int)sizeof(double)), st, a, a.nblocks, 1.0 / nroi, loss);
     return hipGetLastError();
 }
 
 template <int WIN>
-static hipError_t launch_split(const LnccArgs& a, float* loss, double nroi, hipStream_t st)
+static hipError_t launch_split(const LnccLaunch& S, const LnccArgs& a, float* loss, double nroi, hipStream_t st)
 {
     hipLaunchKernelGGL((lncc_kernel<WIN, MODE_ACE, PAD_BORDER, LNCC_ADDR32, 32, 16>), dim3(a.nblocks), dim3(512), 0, st,
                        a);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (a.W <= 64) return launch_xy<WIN, 16, 256>(a, loss, nroi, st);  // 4 W threads, xy_rows(W) rows
-    if (a.W <= 128) return launch_xy<WIN, 16, 512>(a, loss, nroi, st);
-    if (a.W <= 256) return launch_xy<WIN, 16, 1024>(a, loss, nroi, st);
-    return launch_xy<WIN, 8, 1024>(a, loss, nroi, st);
+    if (a.W <= 64) return launch_xy<WIN, 16, 256>(S, a, loss, nroi, st);  // 4 W threads, xy_rows(W) rows
+    if (a.W <= 128) return launch_xy<WIN, 16, 512>(S, a, loss, nroi, st);
+    if (a.W <= 256) return launch_xy<WIN, 16, 1024>(S, a, loss, nroi, st);
+    return launch_xy<WIN, 8, 1024>(S, a, loss, nroi, st);
 }
 
 hipError_t lncc_launch(int mode, int win, int pad, const LnccLaunch& L, const LnccArgs& a, float* loss, double nroi,
@@ -1077,7 +1131,7 @@ hipError_t lncc_launch(int mode, int win, int pad, const LnccLaunch& L, const Ln
         const LnccLaunch S = lncc_plan(a.D, a.H, a.W, win, MODE_ACE);
         LnccArgs b = a;
         b.ntx = S.ntx; b.nty = S.nty; b.zchunk = S.zchunk; b.nblocks = S.nblocks; b.zspan = S.zspan;
-        return win == 7 ? launch_split<7>(b, loss, nroi, st) : launch_split<9>(b, loss, nroi, st);
+        return win == 7 ? launch_split<7>(S, b, loss, nroi, st) : launch_split<9>(S, b, loss, nroi, st);
     }
     if (mode == MODE_FWD) e = launch_mode<MODE_FWD>(win, pad, L, a, st);
     else if (mode == MODE_BWD) e = launch_mode<MODE_BWD>(win, pad, L, a, st);

@@ -29,6 +29,7 @@
 // precision the fused kernel keeps them in), which halves their traffic.
 #include <type_traits>
 
+#include "../../include/ffdp.h"
 #include "device.hpp"
 #include "internal.hpp"
 #include "wide.hpp"
@@ -397,7 +398,9 @@ hipError_t wide_run(int mode, const WideArgs& a, const WidePlan& P, hipStream_t 
 // block, the sum of its first window counted as 8.  w = 11, chunks of 32 ->
 // this rule: 48 x 60 x 80 (30 -> 720 blocks) z 42 -> 14 us, grad 76 -> 11 us;
 // 100 x 120 x 140 (270 -> 900 blocks) z 41 -> 43 us, grad 63 -> 30 us;
-// 160 x 192 x 224 has 960 blocks either way.
+// 160 x 192 x 224 has 960 blocks either way.  A block has a partial sum in the
+// workspace: a volume whose workspace fits the library-owned array with the
+// first rule's blocks gets no more blocks than fit it.
 WidePlan wide_plan(int D, int H, int W)
 {
     WidePlan P;
@@ -409,9 +412,13 @@ WidePlan wide_plan(int D, int H, int W)
     if (want > most) want = most;
     if (want < 1) want = 1;
     if (cols * want < 1024) {
+        const long long zw = (D + want - 1) / want, nb = cols * ((D + zw - 1) / zw);
+        const long long room = FFDP_NOALLOC_MAX_BLOCKS - 8LL * D * H * W;
+        const long long limit = nb <= room ? room : 0x7fffffffLL;
         long long best = -1;
         for (int n = 1; n <= D && n <= 1024; ++n) {
             const int zc = (D + n - 1) / n;
+            if (cols * ((D + zc - 1) / zc) > limit) continue;
             const long long cost = (cols * n + 1023) / 1024 * (zc + 8);
             if (best < 0 || cost < best) { best = cost; want = n; }
         }

@@ -825,7 +825,12 @@ template <int S, bool TWO, bool FROMDY, bool GRAD>
 hipError_t wd_shape(TcArgs& a, hipStream_t st)
 {
     const int nt = (a.Nout + 15) / 16;
-    if ((a.Ca | a.Cb) & 7) return wd_launch<S, S == 1 ? 8 : 4, 2, 4, TWO, false, FROMDY, GRAD>(a, st);
+    // the wide kernel's 16-byte loads to LDS are for channels in eights at 16-byte addresses only: the entry points
+    // take operands at any multiple of 8 bytes, and a load of that width promises nothing there (2 channels at a time
+    // need 4 bytes).  Loads to registers do with 8.
+    const bool a16 = (((uintptr_t)a.xa | (uintptr_t)a.xb | (uintptr_t)a.w) & 15) == 0;
+    if (((a.Ca | a.Cb) & 7) || (S == 1 && !a16))
+        return wd_launch<S, S == 1 ? 8 : 4, 2, 4, TWO, false, FROMDY, GRAD>(a, st);
     if constexpr (S == 1) {
         if (nt == 1) return wd_launch<1, 8, 4, 1, TWO, true, FROMDY, GRAD>(a, st);
         if (nt == 2) return wd_launch<1, 8, 2, 2, TWO, true, FROMDY, GRAD>(a, st);

@@ -57,11 +57,11 @@ struct WgTile {
 
 typedef __attribute__((address_space(3))) s4v lds_s4v;
 
-// 8 voxels of the lane's channel: two transposing reads at p and p + step
-__device__ __forceinline__ bf8v tr8(const unsigned short* p, int step)
+// 8 voxels of the lane's channel: two transposing reads at p and q
+__device__ __forceinline__ bf8v tr8(const unsigned short* p, const unsigned short* q)
 {
     const s4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4v*)(p));
-    const s4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4v*)(p + step));
+    const s4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4v*)(q));
     return __builtin_bit_cast(bf8v, (s8v)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
@@ -82,13 +82,15 @@ template <int S, int RW, bool FROMDY>
 __global__ void __launch_bounds__(256, 2) conv_wgrad_kernel(WgArgs a)
 {
     using T = WgTile<S, RW>;
-    __shared__ __attribute__((aligned(16))) unsigned char lds[T::LDS];
+    __shared__ __attribute__((aligned(16))) unsigned char lds[T::LDS + 16];
     unsigned short* const xsl = reinterpret_cast<unsigned short*>(lds);  // [2][XS]
     unsigned short* const psl = xsl + 2 * T::XS;                         // [2][PS]
+    unsigned short* const zeros = psl + 2 * T::PS;                       // 8 bytes
     const ConvGeom& g = a.g;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int li = lane & 15, kg = lane >> 4;
     const int Cin = g.Ca + g.Cb;
+    if (tid < 4) zeros[tid] = 0;
     // the items of one chunk share its voxels: next to each other, on one XCD
     const int bid = xcd_remap(blockIdx.x, a.nblocks);
     const int item = bid % a.items, chunk = bid / a.items;
@@ -130,6 +132,11 @@ __global__ void __launch_bounds__(256, 2) conv_wgrad_kernel(WgArgs a)
         const int n = (int)(q / a.p.nz);
         const int z1 = min(g.Do, z0 + a.p.zlen);
         const int nk = S * (z1 - z0 - 1) + 3;  // input slices S z0 - 1 ..
+        // Rows and columns past the output have P = 0, but the first of each would still meet the input's last row or
+        // column (tap 0), and 0 times an infinite value is not 0: such a row is skipped, such columns of X are read
+        // from zeros.
+        const int nrow = g.Ho - y0 - __builtin_amdgcn_readfirstlane(wave) * RW;
+        const bool past0 = x0 + 8 * kg + (li >> 2) >= g.Wo, past1 = x0 + 8 * kg + (li >> 2) + 4 >= g.Wo;
 
         // this thread's units of a slice: voxel offset in the slice (-1: outside) and LDS slot
         int xv[T::NX], pv[T::NP];
@@ -218,7 +225,7 @@ __global__ void __launch_bounds__(256, 2) conv_wgrad_kernel(WgArgs a)
                     const unsigned short* const pb = psl + (k & 1) * T::PS + poff;
 #pragma unroll
                     for (int r = 0; r < RW; ++r) {
-                        P[0][r] = tr8(pb + r * WG_X * 16, 64);
+                        P[0][r] = tr8(pb + r * WG_X * 16, pb + r * WG_X * 16 + 64);
                         if (it == 0) accb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(P[0][r], ones, accb, 0, 0, 0);
                     }
                 }
@@ -238,7 +245,10 @@ __global__ void __launch_bounds__(256, 2) conv_wgrad_kernel(WgArgs a)
                 const unsigned short* const rp = xb + (ups ? (row + 1) >> 1 : row) * xpitch;
                 bf8v X[3];
 #pragma unroll
-                for (int dx = 0; dx < 3; ++dx) X[dx] = tr8(rp + xoff[dx], xstep[dx]);
+                for (int dx = 0; dx < 3; ++dx) {
+                    const unsigned short* const p = rp + xoff[dx];
+                    X[dx] = tr8(dx == 0 && past0 ? zeros : p, dx == 0 && past1 ? zeros : p + xstep[dx]);
+                }
 #pragma unroll
                 for (int dz = 0; dz < 3; ++dz) {
                     if (!use[dz]) continue;
@@ -246,7 +256,7 @@ __global__ void __launch_bounds__(256, 2) conv_wgrad_kernel(WgArgs a)
 #pragma unroll
                     for (int yo = 0; yo < RW; ++yo) {
                         const int dyy = r - S * yo;
-                        if (dyy < 0 || dyy > 2) continue;
+                        if (dyy < 0 || dyy > 2 || (dyy == 0 && yo >= nrow)) continue;
 #pragma unroll
                         for (int dx = 0; dx < 3; ++dx)
                             acc[dz][dyy][dx] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(P[d][yo], X[dx],

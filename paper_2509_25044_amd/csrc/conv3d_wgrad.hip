@@ -78,7 +78,9 @@ struct WgArgs {
     int tna, items, nblocks;  // channel tiles of part a; (input, output) tile pairs
 };
 
-template <int S, int RW, bool FROMDY>
+// CUT: the output's width is not a multiple of 32 (the reads that clear the
+// columns past it cost 1 to 2% at stride 1)
+template <int S, int RW, bool FROMDY, bool CUT>
 __global__ void __launch_bounds__(256, 2) conv_wgrad_kernel(WgArgs a)
 {
     using T = WgTile<S, RW>;
@@ -87,7 +89,7 @@ __global__ void __launch_bounds__(256, 2) conv_wgrad_kernel(WgArgs a)
     unsigned short* const psl = xsl + 2 * T::XS;                         // [2][PS]
     unsigned short* const zeros = psl + 2 * T::PS;                       // 8 bytes
     const ConvGeom& g = a.g;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 15, kg = lane >> 4;
     const int Cin = g.Ca + g.Cb;
     if (tid < 4) zeros[tid] = 0;
@@ -135,8 +137,9 @@ __global__ void __launch_bounds__(256, 2) conv_wgrad_kernel(WgArgs a)
         // Rows and columns past the output have P = 0, but the first of each would still meet the input's last row or
         // column (tap 0), and 0 times an infinite value is not 0: such a row is skipped, such columns of X are read
         // from zeros.
-        const int nrow = g.Ho - y0 - __builtin_amdgcn_readfirstlane(wave) * RW;
+        const int nrow = g.Ho - y0 - wave * RW;
         const bool past0 = x0 + 8 * kg + (li >> 2) >= g.Wo, past1 = x0 + 8 * kg + (li >> 2) + 4 >= g.Wo;
+        const int pitch0 = past0 ? 0 : xpitch, pitch1 = past1 ? 0 : xpitch;
 
         // this thread's units of a slice: voxel offset in the slice (-1: outside) and LDS slot
         int xv[T::NX], pv[T::NP];
@@ -215,6 +218,8 @@ __global__ void __launch_bounds__(256, 2) conv_wgrad_kernel(WgArgs a)
                 if (has_p(k + 1)) load_p(z0 + (k + 1) / S);
             }
             const unsigned short* const xb = xsl + (k & 1) * T::XS;
+            const unsigned short* const c0 = past0 ? zeros : xb + xoff[0];  // columns of shift 0
+            const unsigned short* const c1 = past1 ? zeros : xb + xoff[0] + xstep[0];
             if (k % S == 0) {  // a new output slice (or the end: the ring still moves)
 #pragma unroll
                 for (int r = 0; r < RW; ++r) {
@@ -242,12 +247,14 @@ __global__ void __launch_bounds__(256, 2) conv_wgrad_kernel(WgArgs a)
             for (int r = 0; r < XR; ++r) {
                 // stride 1: input row RW wave + r (coarse (. + 1) / 2); stride 2: 2 wave + r
                 const int row = S * RW * wave + r;
-                const unsigned short* const rp = xb + (ups ? (row + 1) >> 1 : row) * xpitch;
+                const int urow = ups ? (row + 1) >> 1 : row;
+                const unsigned short* const rp = xb + urow * xpitch;
                 bf8v X[3];
 #pragma unroll
                 for (int dx = 0; dx < 3; ++dx) {
                     const unsigned short* const p = rp + xoff[dx];
-                    X[dx] = tr8(dx == 0 && past0 ? zeros : p, dx == 0 && past1 ? zeros : p + xstep[dx]);
+                    X[dx] = CUT && dx == 0 ? tr8(c0 + __mul24(urow, pitch0), c1 + __mul24(urow, pitch1))
+                                           : tr8(p, p + xstep[dx]);
                 }
 #pragma unroll
                 for (int dz = 0; dz < 3; ++dz) {
@@ -333,6 +340,13 @@ __global__ void __launch_bounds__(256) reduce_parts_kernel(const float* __restri
 
 constexpr int WG_RW1 = 2, WG_RW2 = 1;  // output rows per wave, stride 1 and 2
 
+template <int S, int RW, bool FROMDY>
+void wgrad_kernel_launch(const WgArgs& a, dim3 grid, dim3 block, hipStream_t st)
+{
+    if (a.g.Wo % WG_X) hipLaunchKernelGGL((conv_wgrad_kernel<S, RW, FROMDY, true>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((conv_wgrad_kernel<S, RW, FROMDY, false>), grid, block, 0, st, a);
+}
+
 int wg_items(const ConvGeom& g)
 {
     return ((g.Ca + 15) / 16 + (g.Cb + 15) / 16) * ((g.Cout + 15) / 16);
@@ -378,11 +392,11 @@ hipError_t conv_wgrad_launch(const ConvGeom& g, const unsigned short* xa, const 
     a.nblocks = (int)nb;
     const dim3 grid((unsigned)nb), block(256);
     if (g.stride == 1) {
-        if (pbf) hipLaunchKernelGGL((conv_wgrad_kernel<1, WG_RW1, false>), grid, block, 0, st, a);
-        else hipLaunchKernelGGL((conv_wgrad_kernel<1, WG_RW1, true>), grid, block, 0, st, a);
+        if (pbf) wgrad_kernel_launch<1, WG_RW1, false>(a, grid, block, st);
+        else wgrad_kernel_launch<1, WG_RW1, true>(a, grid, block, st);
     } else {
-        if (pbf) hipLaunchKernelGGL((conv_wgrad_kernel<2, WG_RW2, false>), grid, block, 0, st, a);
-        else hipLaunchKernelGGL((conv_wgrad_kernel<2, WG_RW2, true>), grid, block, 0, st, a);
+        if (pbf) wgrad_kernel_launch<2, WG_RW2, false>(a, grid, block, st);
+        else wgrad_kernel_launch<2, WG_RW2, true>(a, grid, block, st);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -172,10 +172,7 @@ size_t lncc_ws(const ffdp_grid* g, int window)
     if (window > LNCC_FUSED_MAX_WINDOW) return wide_ws_bytes((int)g->D, (int)g->H, (int)g->W) + 16;
     return (size_t)lncc_max_blocks((int)g->D, (int)g->H, (int)g->W, window) * sizeof(double) + 16;
 }
-unsigned* lncc_flag(void* ws, const ffdp_grid* g, int window)
-{
-    return reinterpret_cast<unsigned*>(static_cast<char*>(ws) + lncc_ws(g, window) - 16);
-}
+unsigned* lncc_flag(void* ws, size_t need) { return reinterpret_cast<unsigned*>(static_cast<char*>(ws) + need - 16); }
 
 // the B^2 histogram, its NaN flag, the checked-mode flag
 size_t mi_ws(const ffdp_mi_params* p) { return ((size_t)p->bins * p->bins + 2) * sizeof(unsigned long long); }
@@ -185,14 +182,14 @@ unsigned* mi_flag(void* ws, const ffdp_mi_params* p)
 }
 
 int lncc_common(const float* F, const float* M, const float* u, const ffdp_grid* g, const ffdp_lncc_params* p,
-                void* ws, size_t ws_bytes, int mode, LnccArgs& a, LnccLaunch& L)
+                void* ws, size_t ws_bytes, int mode, LnccArgs& a, LnccLaunch& L, size_t& need)
 {
     int s = check_grid(g);
     if (s) return s;
     if ((s = check_lncc(p))) return s;
     if ((s = check_ptrs("F,M", 2, (const void*)F, (const void*)M))) return s;
     if ((s = check_opt_ptr(u, "u"))) return s;
-    const size_t need = lncc_ws(g, p->window);
+    need = lncc_ws(g, p->window);
     if (!ws || ws_bytes < need)
         return fail(FFDP_ERR_WORKSPACE, "workspace of %zu bytes required (got %zu%s)", need, ws_bytes,
                     ws ? "" : ", NULL");
@@ -348,11 +345,12 @@ int ffdp_warp_lncc_fwd(const float* F, const float* M, const float* u, const ffd
 {
     LnccArgs a;
     LnccLaunch L;
-    int s = lncc_common(F, M, u, g, p, ws, ws_bytes, 0, a, L);
+    size_t need;
+    int s = lncc_common(F, M, u, g, p, ws, ws_bytes, 0, a, L, need);
     if (s) return s;
     if ((s = check_ptrs("loss", 1, (const void*)loss))) return s;
     hipStream_t st = (hipStream_t)stream;
-    unsigned* flag = lncc_flag(ws, g, p->window);
+    unsigned* flag = lncc_flag(ws, need);
     if (p->check_finite && (s = start_checked(F, M, u, g, nullptr, flag, st))) return s;
     if (p->window > LNCC_FUSED_MAX_WINDOW)
         s = hip_status(lncc_wide_launch(0, p->window, p->pad_mode, a, ws, loss, roi_voxels(g), st),
@@ -368,7 +366,8 @@ int ffdp_warp_lncc_bwd(const float* F, const float* M, const float* u, const ffd
 {
     LnccArgs a;
     LnccLaunch L;
-    int s = lncc_common(F, M, u, g, p, ws, ws_bytes, (p && p->ants_approx) ? 2 : 1, a, L);
+    size_t need;
+    int s = lncc_common(F, M, u, g, p, ws, ws_bytes, (p && p->ants_approx) ? 2 : 1, a, L, need);
     if (s) return s;
     if ((s = check_ptrs("grad_u", 1, (const void*)grad_u))) return s;
     if ((s = check_opt_ptr(grad_scale, "grad_scale"))) return s;
@@ -377,7 +376,7 @@ int ffdp_warp_lncc_bwd(const float* F, const float* M, const float* u, const ffd
     a.grad_scale = grad_scale;
     const int mode = p->ants_approx ? 2 : 1;
     hipStream_t st = (hipStream_t)stream;
-    unsigned* flag = lncc_flag(ws, g, p->window);
+    unsigned* flag = lncc_flag(ws, need);
     if (p->check_finite && (s = start_checked(F, M, u, g, grad_scale, flag, st))) return s;
     if (p->window > LNCC_FUSED_MAX_WINDOW)
         s = hip_status(lncc_wide_launch(mode, p->window, p->pad_mode, a, ws, loss, roi_voxels(g), st),

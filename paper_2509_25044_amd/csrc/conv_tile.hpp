@@ -82,6 +82,7 @@ inline hipError_t tc_plan(TcArgs& a, int Do, int Ho, int Wo, int YT, int WN, int
         if (n != nz) continue;
         const long long cost = ((cols * n + slots - 1) / slots) * (zl + 1);
         if (best < 0 || cost < best) { best = cost; a.zlen = zl; a.nz = n; }
+        if (cols * (Do + n) >= best * slots) break;  // no later count can be below that / slots
     }
     const long long nb = cols * a.nz;
     if (nb > 0x7fffffffLL) return hipErrorInvalidValue;

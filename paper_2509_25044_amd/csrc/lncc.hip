@@ -995,12 +995,16 @@ LnccLaunch lncc_plan(int D, int H, int W, int win, int mode)
     const long long slots = 256LL * (L.nt >= 1024 ? 1 : ((win <= 5 || mode == MODE_ACE || mode == MODE_FWD) ? 2 : 1));
     long long best = -1;
     int bc = 1;
-    for (int c = 1; c <= D && (c <= 64 || tiles * c <= slots); ++c) {
+    for (int c = 1, last = 0; c <= D && (c <= 64 || tiles * c <= slots); ++c) {
         const int zc = (D + c - 1) / c;
+        if (zc == last) continue;  // the same chunks as before
+        last = zc;
         const int nc = (D + zc - 1) / zc;
         const long long rounds = (tiles * nc + slots - 1) / slots;
         const long long cost = rounds * (zc + 2 * RZ);
         if (best < 0 || cost < best) { best = cost; bc = c; }
+        // no later count can be below tiles (D + 2 RZ nc) / slots: a plan 0.4 -> 0.1 us
+        if (tiles * (D + 2LL * RZ * nc) >= best * slots) break;
     }
     L.zchunk = (D + bc - 1) / bc;
     L.nchunks = (D + L.zchunk - 1) / L.zchunk;
@@ -1040,10 +1044,11 @@ static long long xy_lds(int win, int RB, int W, const LnccLaunch& S)
 // fused (64 x 300 x 70, w = 7: 99 against 131 us), others split (160 x 192 x
 // 224: w = 7 187 against 236, w = 9 254 against 286; 40 x 48 x 56, w = 7: 36
 // against 50).  Windows 3 and 5 are faster fused everywhere but on toy sizes.
-static bool lncc_split(int D, int H, int W, int win, int pad)
+// B: the one kernel's plan; S: receives the first half's.
+static bool lncc_split(int D, int H, int W, int win, int pad, const LnccLaunch& B, LnccLaunch& S)
 {
     if (win < 7 || pad != PAD_BORDER || W > LNCC_XY_MAX_W) return false;
-    const LnccLaunch S = lncc_plan(D, H, W, win, MODE_ACE), B = lncc_plan(D, H, W, win, MODE_BWD);
+    S = lncc_plan(D, H, W, win, MODE_ACE);
     if (S.addr != LNCC_ADDR32 || xy_lds(win, xy_rows(W), W, S) > 160 * 1024) return false;
     const int halo = 2 * (win - 1), RB = xy_rows(W);
     const double fused = (win == 7 ? 4.6 : 4.1) * ((B.nblocks + 255) / 256) * (B.zchunk + halo);
@@ -1127,8 +1132,8 @@ hipError_t lncc_launch(int mode, int win, int pad, const LnccLaunch& L, const Ln
                        hipStream_t st)
 {
     hipError_t e;
-    if (mode == MODE_BWD && lncc_split(a.D, a.H, a.W, win, pad)) {
-        const LnccLaunch S = lncc_plan(a.D, a.H, a.W, win, MODE_ACE);
+    LnccLaunch S;
+    if (mode == MODE_BWD && lncc_split(a.D, a.H, a.W, win, pad, L, S)) {
         LnccArgs b = a;
         b.ntx = S.ntx; b.nty = S.nty; b.zchunk = S.zchunk; b.nblocks = S.nblocks; b.zspan = S.zspan;
         return win == 7 ? launch_split<7>(S, b, loss, nroi, st) : launch_split<9>(S, b, loss, nroi, st);

@@ -416,11 +416,14 @@ WidePlan wide_plan(int D, int H, int W)
         const long long room = FFDP_NOALLOC_MAX_BLOCKS - 8LL * D * H * W;
         const long long limit = nb <= room ? room : 0x7fffffffLL;
         long long best = -1;
-        for (int n = 1; n <= D && n <= 1024; ++n) {
+        for (int n = 1, last = 0; n <= D && n <= 1024; ++n) {
             const int zc = (D + n - 1) / n;
+            if (zc == last) continue;
+            last = zc;
             if (cols * ((D + zc - 1) / zc) > limit) continue;
             const long long cost = (cols * n + 1023) / 1024 * (zc + 8);
             if (best < 0 || cost < best) { best = cost; want = n; }
+            if (cols * (D + 8LL * n) >= best * 1024) break;  // no later count can be below that / 1024
         }
     }
     P.zchunk = (int)((D + want - 1) / want);

@@ -767,6 +767,7 @@ static void mi_hist_launch(const MiArgs& a0, int pad, unsigned long long* hist, 
         const int zc = (rz + c - 1) / c, n = (rz + zc - 1) / zc;
         const long long cost = ((tiles * n + slots - 1) / slots) * (zc + 8);
         if (best < 0 || cost < best) { best = cost; a.zchunk = zc; a.nblocks = (int)(tiles * n); }
+        if (tiles * (rz + 8LL * n) >= best * slots) break;  // no later count can be below that / slots
     }
     if (a.ngroups == 1) mi_hist_pad<HARD, AFF, TYB, false>(a, pad, lds, hist, flag, st);
     else mi_hist_pad<HARD, AFF, TYB, true>(a, pad, lds, hist, flag, st);

@@ -177,10 +177,13 @@ static hipError_t smooth_dispatch(const float* in, float* out, int D, int H, int
     if (chunks < 1) chunks = 1;
     if ((long long)tiles * channels * chunks < 1024) {
         long long best = -1;
-        for (int c = 1; c <= D && c <= 1024; ++c) {
+        for (int c = 1, last = 0; c <= D && c <= 1024; ++c) {
             const int zc = (D + c - 1) / c, n = (D + zc - 1) / zc;
+            if (zc == last) continue;
+            last = zc;
             const long long cost = ((long long)tiles * channels * n + 1023) / 1024 * (zc + 2 * R);
             if (best < 0 || cost < best) { best = cost; chunks = n; }
+            if ((long long)tiles * channels * (D + 2LL * R * n) >= best * 1024) break;  // no later cost is below that / 1024
         }
     }
     const int zchunk = (D + chunks - 1) / chunks;

@@ -330,11 +330,13 @@ __device__ __forceinline__ void ace_reference(const float* __restrict__ F, const
 // by its launch bound.  The forward at w = 3 would fit three blocks to a CU,
 // which leaves the last round of the plan's chunks, cut for two, to few of them:
 // held to two (320 x 320 x 320: 331 -> 298 us; planned for three 339 us, and 512
-// x 512 x 512 1279 against 1117 us).  ADDR: see ld().
+// x 512 x 512 1279 against 1117 us; 1040 x 1040 x 1040 11.5 -> 10.7 ms, without a
+// displacement 6.4 -> 6.7).  Not with zero padding, whose 62 VGPRs let four in (320
+// x 320 x 320: 355 us, held to two 421).  ADDR: see ld().
 template <int WIN, int MODE, int PAD, int ADDR, int TX_, int TY_>
 __global__ void __launch_bounds__(TX_ * TY_)
     __attribute__((amdgpu_waves_per_eu((TX_ * TY_ >= 1024 || WIN <= 5 || MODE == MODE_ACE || MODE == MODE_FWD) ? 4 : 2,
-                                         WIN == 3 && MODE == MODE_FWD ? 5 : 8)))
+                                         WIN == 3 && MODE == MODE_FWD && PAD == PAD_BORDER ? 5 : 8)))
 lncc_kernel(LnccArgs a)
 {
     using T = LnccTile<WIN, MODE, TX_, TY_>;

@@ -994,7 +994,11 @@ LnccLaunch lncc_plan(int D, int H, int W, int win, int mode)
     // chunks of a slice or two: the halo slices are sampled again by CUs that
     // would stand idle (40 x 48 x 56, w = 7: 148 -> 52 us against chunks of at
     // least 16 slices).
-    const long long slots = 256LL * (L.nt >= 1024 ? 1 : ((win <= 5 || mode == MODE_ACE || mode == MODE_FWD) ? 2 : 1));
+    // Two of the 512-thread blocks up to w = 5, for the forward pass and MODE_ACE,
+    // and for the ANTs gradient at w = 7 (78 KB of LDS; planned for one: 160 x 192 x
+    // 224 113 against 95 us, with zero padding 169 against 119), else one.
+    const bool two = win <= 5 || mode == MODE_FWD || mode == MODE_ACE || (mode == MODE_ANTS && win == 7);
+    const long long slots = 256LL * (L.nt < 1024 && two ? 2 : 1);
     long long best = -1;
     int bc = 1;
     for (int c = 1, last = 0; c <= D && (c <= 64 || tiles * c <= slots); ++c) {

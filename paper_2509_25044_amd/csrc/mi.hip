@@ -805,13 +805,14 @@ hipError_t mi_fwd_launch(const MiArgs& a0, int hard, int pad, unsigned long long
     // LDS histogram copies: at most 4 and at most 79 KB (two blocks per CU).
     // u64 for the Parzen histogram, rows of mi_hist_pitch(B) entries: 4
     // copies up to 47 bins, 2 up to 68, 1 up to 98, then see mi_hist_launch;
-    // u32 counts of the approximate estimator: within 66 KB up to 128 bins, one
-    // copy up to 199; larger counts are added straight into the global
-    // histogram (ncopy = 0).
-    const size_t budget = hard != 2 ? 80896 : a.bins <= 128 ? 67584 : MI_LDS_HIST;
+    // u32 counts of the approximate estimator: copies within 66 KB up to 129
+    // bins, one up to 199 (a second would leave one block to a CU: 129 bins at 320
+    // x 320 x 320 654 us with one, 937 with two); larger counts are added straight
+    // into the global histogram (ncopy = 0).
+    const size_t budget = hard != 2 ? 80896 : 67584;
     const size_t one = hard == 2 ? (size_t)(a.bins * a.bins + 1) * sizeof(unsigned int)
                                  : (size_t)(a.bins * mi_hist_pitch(a.bins) + 1) * sizeof(unsigned long long);
-    a.ncopy = one <= budget ? 1 : 0;
+    a.ncopy = one <= (hard != 2 ? budget : (size_t)MI_LDS_HIST) ? 1 : 0;
     while (a.ncopy && a.ncopy < 4 && 2 * a.ncopy * one <= budget) a.ncopy *= 2;
     const int BB = a.bins * a.bins;
     unsigned long long* flag = hist + BB;

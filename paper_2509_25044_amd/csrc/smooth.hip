@@ -18,7 +18,9 @@
 //     registers for the z filter, whose output is written to HBM.
 // Two barriers per slice (the write of step 1 and the x outputs of step 3).
 // HBM traffic is one read and one write per element plus the z halo of each
-// chunk (2R slices per chunk of at least 32).
+// chunk: 2R slices per chunk of at least 32, where that makes blocks enough for
+// the chip; small volumes are cut into chunks of down to one slice, whose halos
+// come from the caches.
 //
 // The ADAM variant applies the optimiser step to (x, m, v) with the smoothed
 // value as the gradient where the plain kernel would store it: the smoothed
@@ -168,22 +170,32 @@ static hipError_t smooth_dispatch(const float* in, float* out, int D, int H, int
     const int ntx = (W + SM_TX - 1) / SM_TX, nty = (H + SM_TY - 1) / SM_TY;
     const int tiles = ntx * nty;
     // About 2048 blocks in chunks of at least 32 slices; where that leaves the
-    // chip idle (small volumes), the chunk count with the fewest rounds of 1024
+    // chip idle (small volumes), the chunk count with the fewest rounds of
     // resident blocks times the slices of a block, its 2R halo slices included
     // (40 x 48 x 56: smoothed Adam step 40 -> 11 us, smoothing 19 -> 7 us).
+    // Smoothing alone is held by the memory from 512 blocks on: 30 x 400 x 400, R
+    // = 2, 35 us with 525 blocks, 39 with 1575; 160 x 192 x 224, R = 3, 58 with 720,
+    // 61 with 1008.  The optimiser step waits longer per slice: 160 x 192 x 224, R =
+    // 2, 155 us with 720 blocks, 128 with 1152; from 750 on it gains nothing (181 x
+    // 217 x 181, R = 3, 238 with 756, 242 with 1008).  Blocks of its kernel that fit
+    // a CU: 5 up to R = 2, 4, and 3 at R = 6, where a second round costs more than
+    // the shorter chunks save (160 x 192 x 224, 180 us with 720 blocks, 222 with 1008).
+    const long long cols = (long long)tiles * channels;
+    const int enough = ADAM ? 750 : 512;
+    const long long slots = 256 * (ADAM ? (R <= 2 ? 5 : R <= 5 ? 4 : 3) : 4);
     int chunks = (2048 + tiles * channels - 1) / (tiles * channels);
     const int maxchunks = (D + 31) / 32;
     if (chunks > maxchunks) chunks = maxchunks;
     if (chunks < 1) chunks = 1;
-    if ((long long)tiles * channels * chunks < 1024) {
+    if (cols * chunks < enough) {
         long long best = -1;
         for (int c = 1, last = 0; c <= D && c <= 1024; ++c) {
             const int zc = (D + c - 1) / c, n = (D + zc - 1) / zc;
             if (zc == last) continue;
             last = zc;
-            const long long cost = ((long long)tiles * channels * n + 1023) / 1024 * (zc + 2 * R);
+            const long long cost = (cols * n + slots - 1) / slots * (zc + 2 * R);
             if (best < 0 || cost < best) { best = cost; chunks = n; }
-            if ((long long)tiles * channels * (D + 2LL * R * n) >= best * 1024) break;  // no later cost is below that / 1024
+            if (cols * (D + 2LL * R * n) >= best * slots) break;  // no later cost is below that / slots
         }
     }
     const int zchunk = (D + chunks - 1) / chunks;

@@ -47,18 +47,22 @@ namespace ffdp {
 namespace {
 
 // Channels of a launch of the tile kernel: one group of up to 16, one of up to
-// 8, an upsampled part a of up to 32 and a part b of up to 16 (weights
-// resident in LDS for these), or groups of 32 (the last zero-padded; weights
-// read through L2), part a upsampled or not.
-enum { TC_FULL = 0, TC_FULL_UPS = 1, TC_HALF = 2, TC_QUARTER = 3, TC_MIX = 4 };
+// 8 (upsampled or not), an upsampled part a of up to 32 and a part b of up to 16
+// (weights resident in LDS for these), or groups of 32 (the last zero-padded;
+// weights read through L2), part a upsampled or not.
+enum { TC_FULL = 0, TC_FULL_UPS = 1, TC_HALF = 2, TC_QUARTER = 3, TC_MIX = 4, TC_HALF_UPS = 5, TC_QUARTER_UPS = 6 };
 __host__ __device__ constexpr bool tc_resident(int kind) { return kind >= TC_HALF; }
 
 // a step's K pattern by its part, and whether part a is upsampled
 __host__ __device__ constexpr int tc_type(int kind, int part)
 {
-    return kind == TC_MIX ? (part ? TC_HALF : TC_FULL) : tc_resident(kind) ? kind : TC_FULL;
+    return kind == TC_MIX ? (part ? TC_HALF : TC_FULL)
+           : kind == TC_HALF_UPS ? TC_HALF
+           : kind == TC_QUARTER_UPS ? TC_QUARTER
+           : tc_resident(kind) ? kind : TC_FULL;
 }
-__host__ __device__ constexpr bool tc_ups(int kind) { return kind == TC_MIX || kind == TC_FULL_UPS; }
+__host__ __device__ constexpr bool tc_thin(int kind) { return tc_resident(kind) && kind != TC_MIX; }  // part a alone
+__host__ __device__ constexpr bool tc_ups(int kind) { return kind == TC_FULL_UPS || kind >= TC_MIX; }
 __host__ __device__ constexpr int tc_frags(int type) { return type == TC_FULL ? 27 : type == TC_HALF ? 15 : 9; }
 
 struct TcGroup {
@@ -81,7 +85,7 @@ struct TcTile {
     {
         return (tc_ups(KIND) && part == 0 ? UXW * UXH : XW * XH) * (tc_type(KIND, part) == TC_FULL ? 4 : 2);
     }
-    static constexpr int UA = units(0), UB = units(1);
+    static constexpr int UA = units(0), UB = tc_thin(KIND) ? 0 : units(1);
     // v / w = v * div(w) >> 16 for every staged v
     static constexpr int div(int w) { return (65536 + w - 1) / w; }
     static constexpr bool div_ok(int w, int n)
@@ -231,7 +235,7 @@ __global__ void __launch_bounds__(64 * WR * WN, 2) conv_tile_kernel(TcArgs a)
     // by the run-time count of groups: with the part a known constant of the
     // step the compiler threads the steps into one another and spills
     auto group = [&](int g) {
-        if (KIND == TC_HALF || KIND == TC_QUARTER || g < a.na) return TcGroup{0, 32 * g, tc_frags(TYPE_A) * g};
+        if (tc_thin(KIND) || g < a.na) return TcGroup{0, 32 * g, tc_frags(TYPE_A) * g};
         return TcGroup{1, 32 * (g - a.na), tc_frags(TYPE_A) * a.na + tc_frags(TYPE_B) * (g - a.na)};
     };
 
@@ -861,6 +865,8 @@ hipError_t tc_dispatch(TcArgs& a, bool ups, hipStream_t st)
             if constexpr (S == 1)
                 if (a.Nout <= 16 && a.Ca % 8 == 0 && a.Cb % 8 == 0 && a.Ca <= 32 && a.Cb > 0 && a.Cb <= 16)
                     return tc_launch<1, 8, 4, 1, TC_MIX, FROMDY, GRAD>(a, st);
+            if (a.Cb == 0 && a.Ca <= 8) return tc_shape<S, TC_QUARTER_UPS, FROMDY, GRAD>(a, st);
+            if (a.Cb == 0 && a.Ca <= 16) return tc_shape<S, TC_HALF_UPS, FROMDY, GRAD>(a, st);
             return wd_shape<S, true, FROMDY, GRAD>(a, st);
         }
     }

@@ -49,9 +49,12 @@ namespace {
 // Channels of a launch of the tile kernel: one group of up to 16, one of up to
 // 8 (upsampled or not), an upsampled part a of up to 32 and a part b of up to 16
 // (weights resident in LDS for these), or groups of 32 (the last zero-padded;
-// weights read through L2), part a upsampled or not.
-enum { TC_FULL = 0, TC_FULL_UPS = 1, TC_HALF = 2, TC_QUARTER = 3, TC_MIX = 4, TC_HALF_UPS = 5, TC_QUARTER_UPS = 6 };
-__host__ __device__ constexpr bool tc_resident(int kind) { return kind >= TC_HALF; }
+// weights read through L2), part a upsampled or not, channels in eights or (4) in
+// fours.
+enum { TC_FULL = 0, TC_FULL_UPS = 1, TC_HALF = 2, TC_QUARTER = 3, TC_MIX = 4, TC_HALF_UPS = 5, TC_QUARTER_UPS = 6,
+       TC_FULL4 = 7, TC_FULL4_UPS = 8 };
+__host__ __device__ constexpr bool tc_resident(int kind) { return kind >= TC_HALF && kind <= TC_QUARTER_UPS; }
+__host__ __device__ constexpr bool tc_full4(int kind) { return kind >= TC_FULL4; }
 
 // a step's K pattern by its part, and whether part a is upsampled
 __host__ __device__ constexpr int tc_type(int kind, int part)
@@ -62,7 +65,7 @@ __host__ __device__ constexpr int tc_type(int kind, int part)
            : tc_resident(kind) ? kind : TC_FULL;
 }
 __host__ __device__ constexpr bool tc_thin(int kind) { return tc_resident(kind) && kind != TC_MIX; }  // part a alone
-__host__ __device__ constexpr bool tc_ups(int kind) { return kind == TC_FULL_UPS || kind >= TC_MIX; }
+__host__ __device__ constexpr bool tc_ups(int kind) { return kind == TC_FULL_UPS || kind == TC_FULL4_UPS || (kind >= TC_MIX && kind <= TC_QUARTER_UPS); }
 __host__ __device__ constexpr int tc_frags(int type) { return type == TC_FULL ? 27 : type == TC_HALF ? 15 : 9; }
 
 struct TcGroup {
@@ -267,7 +270,7 @@ __global__ void __launch_bounds__(64 * WR * WN, 2) conv_tile_kernel(TcArgs a)
         const bool zok = (unsigned)zi < (unsigned)sD;
         const size_t base = ((size_t)bn * sD + (zok ? zi : 0)) * ((size_t)sH * sW) * C;
         const int w = ups ? T::UXW : T::XW, rw = ups ? T::div(T::UXW) : T::div(T::XW);
-        const bool c8 = !RES || KIND == TC_MIX || (C & 7) == 0;
+        const bool c8 = !tc_full4(KIND) && (!RES || KIND == TC_MIX || (C & 7) == 0);
         const int t0 = opaque(tid);
         const gptr z = as_global(&tc_zero);
 #pragma unroll
@@ -331,7 +334,12 @@ __global__ void __launch_bounds__(64 * WR * WN, 2) conv_tile_kernel(TcArgs a)
         auto weight = [&](int f) {
             if (RES) return wl[f * 64];
             const int tap = (f / 3) % 3 * 9 + f % 3 * 3 + f / 9;
-            return ld16(cw < C ? wg + (GRAD ? 26 - tap : tap) * (a.Ca + a.Cb) : as_global(&tc_zero));
+            const gptr p = wg + (GRAD ? 26 - tap : tap) * (a.Ca + a.Cb), z = as_global(&tc_zero);
+            if (tc_full4(KIND)) {
+                const uint2 lo = ld8(cw + 4 <= C ? p : z), hi = ld8(cw + 8 <= C ? p + 4 : z);
+                return make_uint4(lo.x, lo.y, hi.x, hi.y);
+            }
+            return ld16(cw < C ? p : z);
         };
 
         constexpr int NB = TYPE == TC_FULL ? 9 : TYPE == TC_HALF ? 5 : 3;  // blocks of 3 weight fragments
@@ -497,31 +505,26 @@ __global__ void __launch_bounds__(64 * WR * WN, 2) conv_wide_kernel(TcArgs a)
 #pragma unroll
         for (int r = 0; r < RW; ++r) acc[s][r] = f4v{0.f, 0.f, 0.f, 0.f};
 
-    // 64 consecutive LDS units from the lanes' addresses: channel chunk ch of
-    // p (zeros where !ok or past C).  !C8: channel counts that are not
-    // multiples of 8 go 2 channels at a time.
-    // Only the first lim units are written.
+    // C8: units of 8 channels go to LDS directly, 64 of them from the lanes' addresses; p (zeros where nc, the channels
+    // from it on, is not positive).  Only the first lim units are written.
     auto dma = [&](uint4* dst, int lim, auto addr) __attribute__((always_inline)) {
-        const gptr z = as_global(&tc_zero);
         const int lane = opaque(tid & 63);
         gptr p;
         int nc;
-        if (C8) {
-            if (lane < lim) {
-                addr(lane, p, nc);
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(nc > 0 ? p : z),
-                                                 (ldsptr)dst, 16, 0, 0);
-            }
-        } else {
-            for (int j = 0; j < 4; ++j) {
-                const int l = 16 * j + (lane >> 2), c = 2 * (lane & 3);
-                if (l < lim) {
-                    addr(l, p, nc);
-                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(c < nc ? p + c : z),
-                                                     (ldsptr)(dst + 16 * j), 4, 0, 0);
-                }
-            }
+        if (lane < lim) {
+            addr(lane, p, nc);
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(nc > 0 ? p : as_global(&tc_zero)),
+                                             (ldsptr)dst, 16, 0, 0);
         }
+    };
+    // !C8: channel counts that are not multiples of 8, or operands at 8-byte addresses: through registers, two loads of 4
+    // channels to a unit; written to LDS after the products (loads to LDS of 2 channels each took 2 to 5 times as long)
+    constexpr int NW = (9 + WR - 1) / WR;
+    uint4 xq[C8 || FROMDY ? 1 : T::NU], wq[C8 ? 1 : NW];
+    auto unit8 = [&](gptr p, int nc) __attribute__((always_inline)) {
+        const gptr z = as_global(&tc_zero);
+        const uint2 lo = ld8(nc >= 4 ? p : z), hi = ld8(nc >= 8 ? p + 4 : z);
+        return make_uint4(lo.x, lo.y, hi.x, hi.y);
     };
     // What the loads' addresses need of a lane is the same in every step: the
     // channels of its chunk, the voxel of each of its units in a slice (-1
@@ -604,13 +607,18 @@ __global__ void __launch_bounds__(64 * WR * WN, 2) conv_wide_kernel(TcArgs a)
                 uint4 r = make_uint4(0u, 0u, 0u, 0u);
                 if (nc > 0) r = p_from_dy8(a.dy, a.y, a.slope, o, c, C);
                 if (p < nun) xd[p] = r;
-            } else {  // a buffer's last units: lanes past it stay out
+            } else if constexpr (C8) {  // a buffer's last units: lanes past it stay out
                 dma(xd + p0, nun - p0, [&](int l, gptr& p, int& nc) __attribute__((always_inline)) {
                     size_t o;
                     int c;
                     unit(p0 + l, o, c, nc);
                     p = src + o + c;
                 });
+            } else {
+                size_t o;
+                int c, nc;
+                unit(p0 + opaque(tid & 63), o, c, nc);
+                xq[u] = unit8(src + o + c, nc);
             }
         }
     };
@@ -629,11 +637,39 @@ __global__ void __launch_bounds__(64 * WR * WN, 2) conv_wide_kernel(TcArgs a)
                 fetch(wd + (wn * 9 + f) * 64, ok, wg + (size_t)(unsigned)(tap * Cin));
                 continue;
             }
-            dma(wd + (wn * 9 + f) * 64, 64, [&](int l, gptr& p, int& nc) __attribute__((always_inline)) {
+            auto row = [&](int l, gptr& p, int& nc) __attribute__((always_inline)) {
                 const int li = l >> 2, n = n0 + wn * 16 + li, c = c0 + 8 * ((l & 3) ^ ((li >> 1) & 3));
                 nc = n < a.Nout ? C - c : 0;
                 p = as_global(a.w) + ((size_t)n * 27 + tap) * Cin + (pa ? 0 : a.Ca) + c;
-            });
+            };
+            if constexpr (C8) {
+                dma(wd + (wn * 9 + f) * 64, 64, row);
+            } else {
+                gptr p;
+                int nc;
+                row(opaque(tid & 63), p, nc);
+                wq[u] = unit8(p, nc);
+            }
+        }
+    };
+    // !C8: what load_x and load_w have read, to LDS (a unit that was not read holds an older one, which no product takes)
+    auto store_x = [&](uint4* xd, int g) __attribute__((always_inline)) {
+        if constexpr (!C8 && !FROMDY) {
+            const int nun = TWO && g < a.na ? T::UXU : T::XU;
+#pragma unroll
+            for (int u = 0; u < T::NU; ++u) {
+                const int p = (u * (T::NT / 64) + wave) * 64 + (tid & 63);
+                if (p < nun) xd[p] = xq[u];
+            }
+        }
+    };
+    auto store_w = [&](uint4* wd) __attribute__((always_inline)) {
+        if constexpr (!C8) {
+#pragma unroll
+            for (int u = 0; u < NW; ++u) {
+                const int f = u * WR + wr;
+                if (f < 9) wd[(wn * 9 + f) * 64 + (tid & 63)] = wq[u];
+            }
         }
     };
     // Order of the x shifts.  Any will do: results differ by the rounding of the sums.  The gradient takes the centre
@@ -649,6 +685,8 @@ __global__ void __launch_bounds__(64 * WR * WN, 2) conv_wide_kernel(TcArgs a)
 
     load_x(xs, 0, 0);
     load_w(ws, 0, 0, ZO ? 0 : shift(0));
+    store_x(xs, 0);
+    store_w(ws);
     arrive();
     int par = 0, wpar = 0;
     if constexpr (ZO) {
@@ -755,6 +793,8 @@ __global__ void __launch_bounds__(64 * WR * WN, 2) conv_wide_kernel(TcArgs a)
                     }
                     if (di == 2 && last) tc_advance<S, RW, GRAD>(a, acc, k, bn, z0, y0 + wr * RW, x0, n0 + wn * 16);
                 }
+                if (di < 2 || more) store_w(ws + (wpar ^ 1) * T::WB);
+                if (di == 0 && more) store_x(xs + (par ^ 1) * T::XB, gn);
                 wpar ^= 1;
                 arrive();
             }
@@ -771,7 +811,7 @@ hipError_t tc_launch(TcArgs& a, hipStream_t st)
     a.ng = a.na + (a.Cb + 31) / 32;
     a.nfrag = tc_frags(tc_type(KIND, 0)) * a.na + tc_frags(tc_type(KIND, 1)) * (a.ng - a.na);
     // steps alternate the two buffers: the two parts of TC_MIX have one each
-    const int ba = KIND == TC_FULL_UPS && T::buf(1) > T::buf(0) ? T::buf(1) : T::buf(0);
+    const int ba = tc_ups(KIND) && !tc_resident(KIND) && T::buf(1) > T::buf(0) ? T::buf(1) : T::buf(0);
     a.buf[0] = tc_resident(KIND) ? WN * a.nfrag * 64 : 0;
     a.buf[1] = a.buf[0] + ba;
     const int lds = (a.buf[1] + (KIND == TC_MIX ? T::buf(1) : ba)) * 16;
@@ -824,7 +864,8 @@ hipError_t tc_shape(TcArgs& a, hipStream_t st)
         if (nt % 3 == 0 && nt % 4 != 0) return tc_launch<1, 8, 1, 3, KIND, FROMDY, GRAD>(a, st);
         return tc_launch<1, 4, 2, 4, KIND, FROMDY, GRAD>(a, st);
     } else {
-        if (nt <= 2) return tc_launch<2, 2, 4, 2, KIND, FROMDY, GRAD>(a, st);
+        if (nt == 1) return tc_launch<2, 2, 4, 1, KIND, FROMDY, GRAD>(a, st);
+        if (nt == 2) return tc_launch<2, 2, 4, 2, KIND, FROMDY, GRAD>(a, st);
         return tc_launch<2, 4, 2, 4, KIND, FROMDY, GRAD>(a, st);
     }
 }
@@ -837,8 +878,17 @@ hipError_t wd_shape(TcArgs& a, hipStream_t st)
     // take operands at any multiple of 8 bytes, and a load of that width promises nothing there (2 channels at a time
     // need 4 bytes).  Loads to registers do with 8.
     const bool a16 = (((uintptr_t)a.xa | (uintptr_t)a.xb | (uintptr_t)a.w) & 15) == 0;
-    if (((a.Ca | a.Cb) & 7) || (S == 1 && !a16))
-        return wd_launch<S, S == 1 ? 8 : 4, 2, 4, TWO, false, FROMDY, GRAD>(a, st);
+    if (((a.Ca | a.Cb) & 7) || (S == 1 && !a16)) {  // 4 rows to a wave leave registers for the units on their way
+        if constexpr (S == 1) {
+            if (nt == 1) return wd_launch<1, 4, 4, 1, TWO, false, FROMDY, GRAD>(a, st);
+            if (nt == 2) return wd_launch<1, 4, 2, 2, TWO, false, FROMDY, GRAD>(a, st);
+            return wd_launch<1, 4, 2, 4, TWO, false, FROMDY, GRAD>(a, st);
+        } else {
+            constexpr int KIND = TWO ? TC_FULL4_UPS : TC_FULL4;
+            if (nt <= 2) return tc_launch<2, 4, 2, 2, KIND, FROMDY, GRAD>(a, st);
+            return tc_launch<2, 8, 1, 4, KIND, FROMDY, GRAD>(a, st);
+        }
+    }
     if constexpr (S == 1) {
         if (nt == 1) return wd_launch<1, 8, 4, 1, TWO, true, FROMDY, GRAD>(a, st);
         if (nt == 2) return wd_launch<1, 8, 2, 2, TWO, true, FROMDY, GRAD>(a, st);

@@ -853,7 +853,9 @@ hipError_t wd_launch(TcArgs& a, hipStream_t st)
 // layers (several blocks per column).  Thin layers wait for memory, not for
 // the matrix cores: 4 rows per wave leave registers for twice the waves (16 ->
 // 4 channels, batch of 4: 0.54 -> 0.49 ms); with 3 tiles the gradient's
-// stores decide, and 8 rows are faster (16 -> 48: 1.68 against 1.93 ms).
+// stores decide, and 8 rows are faster (16 -> 48: 1.68 against 1.93 ms) on
+// volumes beyond the caches' reach: 160 x 192 x 224 435 against 528 us, but 80 x
+// 96 x 112 59 against 55, 40 x 40 x 40 20.3 against 17.4 (batch 1).
 template <int S, int KIND, bool FROMDY, bool GRAD>
 hipError_t tc_shape(TcArgs& a, hipStream_t st)
 {
@@ -861,7 +863,10 @@ hipError_t tc_shape(TcArgs& a, hipStream_t st)
     if constexpr (S == 1) {
         if (nt == 1) return tc_launch<1, 4, 4, 1, KIND, FROMDY, GRAD>(a, st);
         if (nt == 2) return tc_launch<1, 4, 2, 2, KIND, FROMDY, GRAD>(a, st);
-        if (nt % 3 == 0 && nt % 4 != 0) return tc_launch<1, 8, 1, 3, KIND, FROMDY, GRAD>(a, st);
+        if (nt % 3 == 0 && nt % 4 != 0) {
+            if ((long long)a.N * a.Do * a.Ho * a.Wo > 1 << 20) return tc_launch<1, 8, 1, 3, KIND, FROMDY, GRAD>(a, st);
+            return tc_launch<1, 4, 2, 3, KIND, FROMDY, GRAD>(a, st);
+        }
         return tc_launch<1, 4, 2, 4, KIND, FROMDY, GRAD>(a, st);
     } else {
         if (nt == 1) return tc_launch<2, 2, 4, 1, KIND, FROMDY, GRAD>(a, st);

@@ -367,10 +367,7 @@ ConvWgradPlan conv_wgrad_plan(const ConvGeom& g)
     const int items = wg_items(g);
     const long long want = (2048 + items - 1) / items;
     long long nz = (want + cols - 1) / cols;
-    // chunks of at least 8 slices, or of 2 where those leave CUs without a block (16
-    // -> 16 channels at 8 x 8 x 8: 23 -> 18 us, from fp32 dy 35 -> 19)
-    const int zmin = cols * ((g.Do + 7) / 8) * items < 256 ? 2 : 8;
-    if (nz > (g.Do + zmin - 1) / zmin) nz = (g.Do + zmin - 1) / zmin;
+    if (nz > (g.Do + 7) / 8) nz = (g.Do + 7) / 8;
     p.zlen = (int)((g.Do + nz - 1) / nz);
     p.nz = (g.Do + p.zlen - 1) / p.zlen;
     p.units = cols * p.nz;

@@ -158,6 +158,7 @@ __global__ void __launch_bounds__(256, 2) conv_wgrad_kernel(WgArgs a)
             pv[u] = (v < T::YT * WG_X && X < g.Wo && Y < g.Ho) ? Y * g.Wo + X : -1;
         }
         uint4 xr[T::NX], pr[T::NP];
+        P8 raw[FROMDY ? T::NP : 1];  // dy and y of the units, P once they are written to LDS
         const int c8 = 8 * (tid & 1);
         auto load_x = [&](int k) {
             const int zf = S * z0 - 1 + k;
@@ -175,11 +176,12 @@ __global__ void __launch_bounds__(256, 2) conv_wgrad_kernel(WgArgs a)
 #pragma unroll
             for (int u = 0; u < T::NP; ++u) {
                 pr[u] = make_uint4(0u, 0u, 0u, 0u);
+                if constexpr (FROMDY) raw[u] = P8();
                 if (pv[u] < 0) continue;
                 const size_t o = (base + pv[u]) * g.Cout;
                 const int c = co0 + c8;
                 if constexpr (FROMDY) {
-                    pr[u] = p_from_dy8(a.dy, a.y, a.slope, o, c, g.Cout);
+                    raw[u] = p8_load(a.dy, a.y, o, c, g.Cout);
                 } else {
                     pr[u] = load_c8(a.pbf + o, c, g.Cout);
                 }
@@ -199,6 +201,7 @@ __global__ void __launch_bounds__(256, 2) conv_wgrad_kernel(WgArgs a)
 #pragma unroll
                 for (int u = 0; u < T::NP; ++u) {
                     const int p = tid + 256 * u;
+                    if constexpr (FROMDY) pr[u] = p8_form(raw[u], a.y != nullptr, a.slope);
                     if (p < T::YT * WG_X * 2) *reinterpret_cast<uint4*>(pd + p * 8) = pr[u];
                 }
         };

@@ -77,4 +77,41 @@ __device__ __forceinline__ uint4 p_from_dy8(const float* __restrict__ dy, const 
     return r;
 }
 
+// The same in two steps, so that the loads can be in flight meanwhile: 8
+// channels of dy and y as read (past Cout dy 0 and y 1, so that P is 0 there
+// whatever the slope), then P.
+struct P8 {
+    f32x4_a4 d0 = {0.f, 0.f, 0.f, 0.f}, d1 = {0.f, 0.f, 0.f, 0.f};
+    uint2 y0 = make_uint2(0x3f803f80u, 0x3f803f80u), y1 = make_uint2(0x3f803f80u, 0x3f803f80u);
+};
+__device__ __forceinline__ P8 p8_load(const float* __restrict__ dy, const unsigned short* __restrict__ y, size_t o,
+                                      int c, int Cout)
+{
+    P8 r;
+    if (c < Cout) {
+        r.d0 = *reinterpret_cast<const f32x4_a4*>(dy + o + c);
+        if (y) r.y0 = ld8(y + o + c);
+    }
+    if (c + 4 < Cout) {
+        r.d1 = *reinterpret_cast<const f32x4_a4*>(dy + o + c + 4);
+        if (y) r.y1 = ld8(y + o + c + 4);
+    }
+    return r;
+}
+__device__ __forceinline__ uint2 p4_form(f32x4_a4 d, uint2 y, bool act, float slope)
+{
+    float v[4] = {d.x, d.y, d.z, d.w};
+    if (act) {
+        const unsigned yw[2] = {y.x, y.y};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] *= lrelu_d((unsigned short)(yw[q >> 1] >> (16 * (q & 1))), slope);
+    }
+    return make_uint2(p_pack2(v[0], v[1]), p_pack2(v[2], v[3]));
+}
+__device__ __forceinline__ uint4 p8_form(const P8& r, bool act, float slope)
+{
+    const uint2 lo = p4_form(r.d0, r.y0, act, slope), hi = p4_form(r.d1, r.y1, act, slope);
+    return make_uint4(lo.x, lo.y, hi.x, hi.y);
+}
+
 }  // namespace ffdp

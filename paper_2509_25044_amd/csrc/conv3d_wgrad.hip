@@ -370,7 +370,11 @@ ConvWgradPlan conv_wgrad_plan(const ConvGeom& g)
     const int items = wg_items(g);
     const long long want = (2048 + items - 1) / items;
     long long nz = (want + cols - 1) / cols;
-    if (nz > (g.Do + 7) / 8) nz = (g.Do + 7) / 8;
+    // Chunks of at least 8 slices; of 2 where those make fewer than 8 blocks, each a
+    // chain of its slices (16 -> 16 channels at 8 x 8 x 8: 23.5 -> 18.3 us, from fp32
+    // dy 31 -> 19).
+    const int zmin = cols * ((g.Do + 7) / 8) * items < 8 ? 2 : 8;
+    if (nz > (g.Do + zmin - 1) / zmin) nz = (g.Do + zmin - 1) / zmin;
     p.zlen = (int)((g.Do + nz - 1) / nz);
     p.nz = (g.Do + p.zlen - 1) / p.zlen;
     p.units = cols * p.nz;

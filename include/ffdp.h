@@ -336,17 +336,14 @@ int ffdp_conv3d_act_grad(const float* dy, const uint16_t* y, float slope, int64_
 /* ffdp_conv3d_bwd_data with P given directly: p bf16 [N][Do][Ho][Wo][Cout]
  * (16-byte aligned), e.g. from ffdp_conv3d_act_grad.  Bitwise the same dx
  * as ffdp_conv3d_bwd_data(dy, y, slope, ...) for p = act_grad(dy, y, slope);
- * one 16-byte operand load per lane and K step instead of three plus the
- * conversion. */
+ * an operand of 2 bytes per element is read instead of 6 plus the conversion. */
 int ffdp_conv3d_bwd_data_bf16(const uint16_t* p, const uint16_t* wt, const ffdp_conv_geom* g, float* dx,
                               int32_t accumulate, void* stream);
 
 /* Backward to the weights: dw[co][t][ci] = sum_o P[o][co] X[o*stride + t - 1][ci]
  * and db[co] = sum_o P[o][co] (db may be NULL), fp32, overwritten; the sums
  * over output voxels run in chunks whose partials (caller workspace) are
- * added in a fixed order.  For the stride-2 layers and those with more than
- * 64 output channels the workspace also holds P as bf16 in [Cout][voxel]
- * order (2 bytes per output voxel and channel). */
+ * added in a fixed order, and the workspace holds nothing else. */
 /* ffdp_conv3d_bwd_weight with P given directly: p bf16 [N][Do][Ho][Wo][Cout]
  * (8-byte aligned), e.g. from ffdp_conv3d_act_grad; the same workspace.  The
  * same dw and db, bit for bit, as ffdp_conv3d_bwd_weight(dy, y, slope, ...)

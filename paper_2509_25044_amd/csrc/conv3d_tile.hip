@@ -24,10 +24,12 @@
 // of two rows: 15 steps, 13.5 being the least); one of up to 8 channels takes
 // dx 0, 1, 2 in one step (9 steps).  Lanes that a pattern leaves over multiply
 // zeros by zeros, so an infinite value reaches only the sums it belongs to.
-// Weights are resident in LDS where 27 taps of the layer's channels fit beside
-// the slices (at most 32 + 16 channels).  conv_wide_kernel takes the stride-1
-// layers with more: weights and slices go to LDS directly, a third of a
-// group's weights at a time.
+// Weights are resident in LDS (one part of up to 16 channels, or an upsampled
+// part and a skip for up to 16 output channels) or, at stride 2 with more
+// channels, read through L2.  conv_wide_kernel takes the other stride-1 layers:
+// weights and slices go to LDS a third of a group's weights at a time, directly
+// where channels come in eights.  Which layer takes which is tc_dispatch and
+// wd_shape, at the end.
 //
 // Bound and rates, clinical batch of 4 (ms, against a kernel that gathered
 // both operands per lane from global memory): matrix issue for 48 -> 16 at full
@@ -875,6 +877,11 @@ hipError_t tc_shape(TcArgs& a, hipStream_t st)
     }
 }
 
+// Layers with more channels than the tile kernel's resident weights take: stride 1
+// conv_wide_kernel, stride 2 conv_tile_kernel with weights through L2; each for
+// channels in eights, or in fours (80 x 96 x 112: 20 + 4 -> 16 102 us, 153 with a
+// kernel that gathered per lane, 387 with 4-byte loads to LDS; 12 <- 20 gradient 55,
+// 111, 200; at stride 2 44, 36, 161).
 template <int S, bool TWO, bool FROMDY, bool GRAD>
 hipError_t wd_shape(TcArgs& a, hipStream_t st)
 {
@@ -912,6 +919,11 @@ hipError_t wd_shape(TcArgs& a, hipStream_t st)
     }
 }
 
+// Resident weights: one part of up to 8 or up to 16 channels, upsampled or not (an
+// upsampled one padded to the wide kernel's 32: 4 -> 16 at 80 x 96 x 112 203 us, 20
+// here), or (stride 1) an upsampled part a of up to 32 with a part b of up to 16, in
+// eights, for up to 16 output channels: 27 taps of those fit LDS beside the slices.
+// All else: wd_shape.
 template <int S, bool FROMDY, bool GRAD>
 hipError_t tc_dispatch(TcArgs& a, bool ups, hipStream_t st)
 {

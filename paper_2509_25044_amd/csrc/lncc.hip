@@ -576,7 +576,7 @@ lncc_kernel(LnccArgs a)
                 return;
             }
             __syncthreads();
-            // ---- stage B: x-window, 2 outputs per thread ----
+            // ---- stage B: x-window, 4 outputs of one channel per item ----
             for (int q = tid; q < T::RB; q += NT) {
                 const int row = q / T::NRB, lx0 = 4 * (q - row * T::NRB);  // rows of all channels
                 xwin4<WIN, T::NV, false>(sA + row * X2p + lx0, sB + row * X1p + lx0);
@@ -968,8 +968,8 @@ __global__ void __launch_bounds__(256) lncc_finalize(const double* __restrict__ 
 // output (its 4r halo) and its 167 VGPRs and 96 KB of LDS leave one block of
 // 8 waves per CU; 24 rows sample 2.06 points per output, and one block of
 // 12 waves fits (168 VGPRs, 134 KB): 512^3 adjoint 5.10 -> 4.74 ms, 1040^3
-// 45.6 -> 38.2 ms (4.22 ms now; where lncc_split says so two kernels take its
-// place).  (32 x 32 does not fit the LDS; at w = 5 the two-block
+// 45.6 -> 38.2 ms (512^3 4.36 ms now, by 4-wide x passes; where lncc_split says
+// so two kernels take its place).  (32 x 32 does not fit the LDS; at w = 5 the two-block
 // 32 x 16 layout stays faster than any one-block tile.)
 static void lncc_tile(int win, int mode, int& tx, int& ty)
 {
@@ -1047,9 +1047,14 @@ static long long xy_lds(int win, int RB, int W, const LnccLaunch& S)
 // slice, the first half 3.7 or 4.3 with two blocks on a CU and about 2.2 with
 // one, the second 1.5 per step and 1.4 per 1000 voxels of it, twice that beyond
 // the last-level cache.  So few slices, with long second halves on few CUs, stay
-// fused (64 x 300 x 70, w = 7: 99 against 131 us), others split (160 x 192 x
-// 224: w = 7 187 against 236, w = 9 254 against 286; 40 x 48 x 56, w = 7: 36
-// against 50).  Windows 3 and 5 are faster fused everywhere but on toy sizes.
+// fused (64 x 300 x 70, w = 7: 99 against 131 us), others split.  The constants are
+// from repeated calls on one pair, which find its arrays in the last-level cache
+// up to about 7 million voxels (160 x 192 x 224: w = 7 194 against 236, w = 9 255
+// against 286; 40 x 48 x 56, w = 7: 37 against 50); the split moves 76 bytes a
+// voxel for the fused kernel's 32, but with the caches cold it takes less time
+// still: 234 and 308 us at 160 x 192 x 224, 43 at 40 x 48 x 56, 614 and 750 at 256 x
+// 256 x 256, where the fused kernels of 2-wide x passes took 294 and 415, 156, 707
+// and 866.  Windows 3 and 5 are faster fused everywhere but on toy sizes.
 // B: the one kernel's plan; S: receives the first half's.
 static bool lncc_split(int D, int H, int W, int win, int pad, const LnccLaunch& B, LnccLaunch& S)
 {

@@ -710,9 +710,13 @@ MiLaunch mi_plan(int rz, int ry, int rx)
     const int maxchunks = (rz + 31) / 32;
     if (chunks > maxchunks) chunks = maxchunks;
     if (chunks < 1) chunks = 1;
-    // Fewer than 512 blocks leave CUs idle: chunks down to 4 slices (an 80 x 96
-    // x 112 iteration 76 us with 144 blocks, 58, 56, 58, 60 with 384, 512, 768,
-    // 1024: each block clears and merges a histogram).
+    // Fewer than 512 blocks leave CUs idle: chunks down to 4 slices.  Forward and
+    // adjoint at 32 bins, chunks of at least 32 slices, then for 256, 384, 512, 768
+    // and 1024 blocks at least: 80 x 96 x 112 60 us, 45, 43, 42, 42, 43; 48 x 120 x
+    // 180 56, 56, 47, 43, 43, 46; 100 x 100 x 100 58, 51, 52, 44, 44, 47; 128 x 128
+    // x 96 70, 70, 65, 55, 53, 51; 30 x 200 x 150 at 16 bins 61, 61, 48, 42, 42, 42
+    // (42 is what the calls take on the host).  Each block clears and merges a
+    // histogram.
     if (tiles * chunks < 512) chunks = max(1, min(512 / tiles, (rz + 3) / 4));
     L.zchunk = (rz + chunks - 1) / chunks;
     L.nchunks = (rz + L.zchunk - 1) / L.zchunk;

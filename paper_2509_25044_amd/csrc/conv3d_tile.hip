@@ -457,16 +457,16 @@ __global__ void __launch_bounds__(64 * WR * WN, 2) conv_tile_kernel(TcArgs a)
 // chunks of a voxel) fall in different banks.  Loads go to LDS directly; a
 // sub-step is one x shift of a (slice, group): 9 weight fragments per tile
 // (the next ones are in flight meanwhile) against the wave's input rows.
-template <int S, int RW, int WR, int WN>
+template <int RW, int WR, int WN>
 struct WdTile {
     static constexpr int NT = 64 * WR * WN, YT = WR * RW;
-    static constexpr int XW = S * 15 + 3, XP = S == 1 ? 18 : 34, XH = S * (YT - 1) + 3;
-    static constexpr int UXW = S == 1 ? 10 : 17, UXP = S == 1 ? 10 : 18, UXH = S == 1 ? YT / 2 + 2 : YT + 1;
+    static constexpr int XP = 18, XH = YT + 2;
+    static constexpr int UXP = 10, UXH = YT / 2 + 2;  // of an upsampled part
     static constexpr int XU = XH * XP * 4, UXU = UXH * UXP * 4;  // units of a slice
     static constexpr int XB = (XU > UXU ? XU : UXU);             // ... of a buffer
     static constexpr int WB = WN * 9 * 64;
     static constexpr int LDS = 2 * (XB + WB) * 16;
-    static constexpr int NU = (XU + NT - 1) / NT, NUX = (UXU + NT - 1) / NT, XR = S * (RW - 1) + 3;
+    static constexpr int NU = (XU + NT - 1) / NT, NUX = (UXU + NT - 1) / NT, XR = RW + 2;
     static constexpr int div(int w) { return (65536 + w - 1) / w; }
     static constexpr bool div_ok(int w, int n)
     {
@@ -481,11 +481,11 @@ struct WdTile {
 
 typedef __attribute__((address_space(3))) void* ldsptr;
 
-template <int S, int RW, int WR, int WN, bool TWO, bool C8, bool FROMDY, bool GRAD, bool ZO>
+template <int RW, int WR, int WN, bool TWO, bool C8, bool FROMDY, bool GRAD, bool ZO>
 __global__ void __launch_bounds__(64 * WR * WN, 2) conv_wide_kernel(TcArgs a)
 {
-    using T = WdTile<S, RW, WR, WN>;
-    constexpr int SL = S == 1 ? 3 : 2;
+    using T = WdTile<RW, WR, WN>;
+    constexpr int SL = 3;
     extern __shared__ uint4 lds[];
     uint4* const xs = lds;              // [2][XB]
     uint4* const ws = lds + 2 * T::XB;  // [2][WB]
@@ -498,7 +498,7 @@ __global__ void __launch_bounds__(64 * WR * WN, 2) conv_wide_kernel(TcArgs a)
     const int z0 = (q % a.nz) * a.zlen;
     const int bn = q / a.nz;
     const int nz = min(a.Do, z0 + a.zlen) - z0;
-    const int nk = S * (nz - 1) + 3;
+    const int nk = nz + 2;
     const int Cin = a.Ca + a.Cb;
     const bool active = n0 + wn * 16 < a.Nout && y0 + wr * RW < a.Ho;
     f4v acc[SL][RW];
@@ -546,7 +546,6 @@ __global__ void __launch_bounds__(64 * WR * WN, 2) conv_wide_kernel(TcArgs a)
             const int X = (x0 >> us) - 1 + v - (int)__umul24(vy, w), Y = (y0 >> us) - 1 + vy;
             return p < n && (unsigned)X < (unsigned)sW && (unsigned)Y < (unsigned)sH ? Y * sW + X : -1;
         };
-        static_assert(!FAST || S == 1, "columns of a stride-2 slice are reordered");
 #pragma unroll
         for (int u = 0; u < T::NU; ++u) vox[u] = voxel(u, 0, T::XP, T::div(T::XP), T::XU);
         if constexpr (TWO) {
@@ -582,7 +581,7 @@ __global__ void __launch_bounds__(64 * WR * WN, 2) conv_wide_kernel(TcArgs a)
             return;
         }
         const int sW = a.Wi >> us, sH = a.Hi >> us, sD = a.Di >> us;
-        const int bx = (S * x0 >> us) - 1, by = (S * y0 >> us) - 1, zi = (S * z0 - 1 + k) >> us;
+        const int bx = (x0 >> us) - 1, by = (y0 >> us) - 1, zi = (z0 - 1 + k) >> us;
         const bool zok = (unsigned)zi < (unsigned)sD;
         const size_t base = ((size_t)bn * sD + (zok ? zi : 0)) * ((size_t)sH * sW) * C;
         const int w = ups ? T::UXP : T::XP, rw = ups ? T::div(T::UXP) : T::div(T::XP), nun = ups ? T::UXU : T::XU;
@@ -593,8 +592,7 @@ __global__ void __launch_bounds__(64 * WR * WN, 2) conv_wide_kernel(TcArgs a)
             // voxel, channel offset and number of channels of unit p
             auto unit = [&](int p, size_t& o, int& c, int& nc) __attribute__((always_inline)) {
                 const int v = p >> 2, vy = (int)(__umul24(v, rw) >> 16);
-                int vx = v - (int)__umul24(vy, w);
-                if (S == 2 && !ups) vx = vx < 17 ? 2 * vx : 2 * vx - 33;  // even columns, then odd ones
+                const int vx = v - (int)__umul24(vy, w);
                 const int X = bx + vx, Y = by + vy;
                 c = c0 + 8 * ((p & 3) ^ ((v >> 1) & 3));
                 const bool ok = zok && (unsigned)X < (unsigned)sW && (unsigned)Y < (unsigned)sH;
@@ -633,7 +631,7 @@ __global__ void __launch_bounds__(64 * WR * WN, 2) conv_wide_kernel(TcArgs a)
 #pragma unroll
         for (int u = 0; u < (9 + WR - 1) / WR; ++u) {
             const int f = u * WR + wr;
-            if (f >= 9 || (!ZO && !tc_used<S>(k, f / 3, nz))) continue;  // what no output slice needs is not fetched
+            if (f >= 9 || (!ZO && !tc_used<1>(k, f / 3, nz))) continue;  // what no output slice needs is not fetched
             const int t = ZO ? 9 * d + f : 3 * f + d, tap = GRAD ? 26 - t : t;
             if constexpr (FAST) {
                 fetch(wd + (wn * 9 + f) * 64, ok, wg + (size_t)(unsigned)(tap * Cin));
@@ -735,13 +733,13 @@ __global__ void __launch_bounds__(64 * WR * WN, 2) conv_wide_kernel(TcArgs a)
                                     for (int dy = 0; dy < 3; ++dy)
 #pragma unroll
                                         for (int yo = 0; yo < RW; ++yo)
-                                            acc[tc_slot<S>(s)][yo] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                                as_bf8(w[dy]), as_bf8(X[yo + dy]), acc[tc_slot<S>(s)][yo], 0, 0, 0);
+                                            acc[tc_slot<1>(s)][yo] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                                as_bf8(w[dy]), as_bf8(X[yo + dy]), acc[tc_slot<1>(s)][yo], 0, 0, 0);
                                 }
                         }
                     }
                     if (active && dz == d1 && last)
-                        tc_advance<S, RW, GRAD>(a, acc, k, bn, z0, y0 + wr * RW, x0, n0 + wn * 16);
+                        tc_advance<1, RW, GRAD>(a, acc, k, bn, z0, y0 + wr * RW, x0, n0 + wn * 16);
                     wpar ^= 1;
                     arrive();
                 }
@@ -762,8 +760,8 @@ __global__ void __launch_bounds__(64 * WR * WN, 2) conv_wide_kernel(TcArgs a)
                 uint4 X[T::XR], w[9];
                 if (active) {
                     const int lane = opaque(tid & 63), li = lane & 15, kg = lane >> 4;
-                    const int px = ups ? (S * li + dx + 1) >> 1 : S == 1 ? li + dx : (dx & 1) * 17 + li + (dx >> 1);
-                    const int r0 = S * RW * wr, v0 = px + (ups ? (r0 / 2) * T::UXP : r0 * T::XP);
+                    const int px = ups ? (li + dx + 1) >> 1 : li + dx;
+                    const int r0 = RW * wr, v0 = px + (ups ? (r0 / 2) * T::UXP : r0 * T::XP);
                     int at[4];  // rows r, r + 4, ... share the XOR pattern
 #pragma unroll
                     for (int e = 0; e < 4; ++e) at[e] = 4 * v0 + (kg ^ (((v0 >> 1) + e) & 3));
@@ -784,16 +782,16 @@ __global__ void __launch_bounds__(64 * WR * WN, 2) conv_wide_kernel(TcArgs a)
                 if (active) {
 #pragma unroll
                     for (int dz = 0; dz < 3; ++dz) {
-                        if (tc_used<S>(k, dz, nz)) {
+                        if (tc_used<1>(k, dz, nz)) {
 #pragma unroll
                             for (int dy = 0; dy < 3; ++dy)
 #pragma unroll
                                 for (int yo = 0; yo < RW; ++yo)
-                                    acc[tc_slot<S>(dz)][yo] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                        as_bf8(w[3 * dz + dy]), as_bf8(X[S * yo + dy]), acc[tc_slot<S>(dz)][yo], 0, 0, 0);
+                                    acc[tc_slot<1>(dz)][yo] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                        as_bf8(w[3 * dz + dy]), as_bf8(X[yo + dy]), acc[tc_slot<1>(dz)][yo], 0, 0, 0);
                         }
                     }
-                    if (di == 2 && last) tc_advance<S, RW, GRAD>(a, acc, k, bn, z0, y0 + wr * RW, x0, n0 + wn * 16);
+                    if (di == 2 && last) tc_advance<1, RW, GRAD>(a, acc, k, bn, z0, y0 + wr * RW, x0, n0 + wn * 16);
                 }
                 if (di < 2 || more) store_w(ws + (wpar ^ 1) * T::WB);
                 if (di == 0 && more) store_x(xs + (par ^ 1) * T::XB, gn);
@@ -824,10 +822,10 @@ hipError_t tc_launch(TcArgs& a, hipStream_t st)
     return hipGetLastError();
 }
 
-template <int S, int RW, int WR, int WN, bool TWO, bool C8, bool FROMDY, bool GRAD>
+template <int RW, int WR, int WN, bool TWO, bool C8, bool FROMDY, bool GRAD>
 hipError_t wd_launch(TcArgs& a, hipStream_t st)
 {
-    using T = WdTile<S, RW, WR, WN>;
+    using T = WdTile<RW, WR, WN>;
     a.na = (a.Ca + 31) / 32;
     a.ng = a.na + (a.Cb + 31) / 32;
     const hipError_t e = tc_plan(a, a.Do, a.Ho, a.Wo, T::YT, WN, tc_resident_blocks(T::LDS, T::NT, RW));
@@ -837,14 +835,14 @@ hipError_t wd_launch(TcArgs& a, hipStream_t st)
     // as many as ever and a third or half full (192 -> 64: one 64 x 64 x 64 volume, 1 slice, 70 -> 55 us; 160 x 192 x
     // 224, 2 slices, 107 -> 103 us).  From 3 slices on, reading the rows once per x shift outweighs it.  A single
     // channel tile's rows leave no registers for it.
-    if constexpr (S == 1 && C8 && !FROMDY && WN > 1) {
+    if constexpr (C8 && !FROMDY && WN > 1) {
         if (a.zlen <= 2) {
-            hipLaunchKernelGGL((conv_wide_kernel<S, RW, WR, WN, TWO, C8, FROMDY, GRAD, true>), dim3((unsigned)a.nblocks),
+            hipLaunchKernelGGL((conv_wide_kernel<RW, WR, WN, TWO, C8, FROMDY, GRAD, true>), dim3((unsigned)a.nblocks),
                                dim3(T::NT), T::LDS, st, a);
             return hipGetLastError();
         }
     }
-    hipLaunchKernelGGL((conv_wide_kernel<S, RW, WR, WN, TWO, C8, FROMDY, GRAD, false>), dim3((unsigned)a.nblocks),
+    hipLaunchKernelGGL((conv_wide_kernel<RW, WR, WN, TWO, C8, FROMDY, GRAD, false>), dim3((unsigned)a.nblocks),
                        dim3(T::NT), T::LDS, st, a);
     return hipGetLastError();
 }
@@ -886,15 +884,15 @@ template <int S, bool TWO, bool FROMDY, bool GRAD>
 hipError_t wd_shape(TcArgs& a, hipStream_t st)
 {
     const int nt = (a.Nout + 15) / 16;
-    // the wide kernel's 16-byte loads to LDS are for channels in eights at 16-byte addresses only: the entry points
-    // take operands at any multiple of 8 bytes, and a load of that width promises nothing there (2 channels at a time
-    // need 4 bytes).  Loads to registers do with 8.
+    // The wide kernel's 16-byte loads to LDS are for channels in eights at 16-byte addresses only: the entry points
+    // take operands at any multiple of 8 bytes, and a load of that width promises nothing there.  Loads to registers
+    // do with 8.
     const bool a16 = (((uintptr_t)a.xa | (uintptr_t)a.xb | (uintptr_t)a.w) & 15) == 0;
     if (((a.Ca | a.Cb) & 7) || (S == 1 && !a16)) {  // 4 rows to a wave leave registers for the units on their way
         if constexpr (S == 1) {
-            if (nt == 1) return wd_launch<1, 4, 4, 1, TWO, false, FROMDY, GRAD>(a, st);
-            if (nt == 2) return wd_launch<1, 4, 2, 2, TWO, false, FROMDY, GRAD>(a, st);
-            return wd_launch<1, 4, 2, 4, TWO, false, FROMDY, GRAD>(a, st);
+            if (nt == 1) return wd_launch<4, 4, 1, TWO, false, FROMDY, GRAD>(a, st);
+            if (nt == 2) return wd_launch<4, 2, 2, TWO, false, FROMDY, GRAD>(a, st);
+            return wd_launch<4, 2, 4, TWO, false, FROMDY, GRAD>(a, st);
         } else {
             constexpr int KIND = TWO ? TC_FULL4_UPS : TC_FULL4;
             if (nt <= 2) return tc_launch<2, 4, 2, 2, KIND, FROMDY, GRAD>(a, st);
@@ -902,14 +900,14 @@ hipError_t wd_shape(TcArgs& a, hipStream_t st)
         }
     }
     if constexpr (S == 1) {
-        if (nt == 1) return wd_launch<1, 8, 4, 1, TWO, true, FROMDY, GRAD>(a, st);
-        if (nt == 2) return wd_launch<1, 8, 2, 2, TWO, true, FROMDY, GRAD>(a, st);
+        if (nt == 1) return wd_launch<8, 4, 1, TWO, true, FROMDY, GRAD>(a, st);
+        if (nt == 2) return wd_launch<8, 2, 2, TWO, true, FROMDY, GRAD>(a, st);
         // 6 tiles: three blocks of 2 fill the four SIMDs evenly, two of 3 do not (32 -> 96 gradient: 0.73 against
         // 1.02 ms)
-        if (nt == 6) return wd_launch<1, 8, 2, 2, TWO, true, FROMDY, GRAD>(a, st);
-        if (nt % 3 == 0 && nt % 4 != 0) return wd_launch<1, 8, 1, 3, TWO, true, FROMDY, GRAD>(a, st);
-        if (a.Ho > 8) return wd_launch<1, 8, 2, 4, TWO, true, FROMDY, GRAD>(a, st);
-        return wd_launch<1, 8, 1, 4, TWO, true, FROMDY, GRAD>(a, st);
+        if (nt == 6) return wd_launch<8, 2, 2, TWO, true, FROMDY, GRAD>(a, st);
+        if (nt % 3 == 0 && nt % 4 != 0) return wd_launch<8, 1, 3, TWO, true, FROMDY, GRAD>(a, st);
+        if (a.Ho > 8) return wd_launch<8, 2, 4, TWO, true, FROMDY, GRAD>(a, st);
+        return wd_launch<8, 1, 4, TWO, true, FROMDY, GRAD>(a, st);
     } else {
         // half the taps per input slice are too little work for a barrier per x shift: one step per group, weights
         // through L2 (32 -> 64, batch of 4: 0.11 against 0.19 ms)
